@@ -286,18 +286,20 @@ __device__ __forceinline__ void solve_box(const BoxJob &J, const BoxRun &R, BoxS
     };
 
     // vcycle(H, nl, 0) of the per-level path, written out for one to three levels
-    auto vcycle = [&](double w) __attribute__((always_inline)) {
+    auto vcycle = [&](bool damped) __attribute__((always_inline)) {
+        const double w = step_factor(damped, false), wc = step_factor(damped, true);
+        const int csweeps = coarsest_sweeps(damped);
         if constexpr (NL == 1) {
-            smooth(L0, R.csweeps, w);
+            smooth(L0, csweeps, wc);
         } else {
             smooth(L0, R.nu1, w);
             restrict_level(L0, L1);
             if constexpr (NL == 2) {
-                smooth(L1, R.csweeps, w);
+                smooth(L1, csweeps, wc);
             } else {
                 smooth(L1, R.nu1, w);
                 restrict_level(L1, L2);
-                smooth(L2, R.csweeps, w);
+                smooth(L2, csweeps, wc);
                 prolong_level(L1, L2);
                 smooth(L1, R.nu2, w);
             }
@@ -336,21 +338,18 @@ __device__ __forceinline__ void solve_box(const BoxJob &J, const BoxRun &R, BoxS
             const double rr = residual_sumsq();
             sn2 = rr < 1e-300 ? 1e-300 : rr; // std::max(rr, 1e-300)
         }
-        double w = 1.0;
-        if (R.damped_start) {
-            w = kDampedStep;
-            out.damped_from = 1;
-        }
+        bool damped = R.damped_start != 0;
+        if (damped) out.damped_from = 1;
         // the cycles of relax_patch's drive(), twice when the safeguard asks
         for (int pass = 0; pass < 2; ++pass) {
             const bool may_restart = pass == 0;
             CycleMonitor m{R.tol, R.maxc};
-            m.damped = w != 1.0;
+            m.damped = damped;
             m.start(sqrt(residual_sumsq() / sn2));
             bool restart = false;
             int code = 0;
             while (out.cycles < m.maxc && !m.converged()) {
-                vcycle(w);
+                vcycle(damped);
                 ++out.cycles;
                 const double r = sqrt(residual_sumsq() / sn2);
                 const bool again = m.record(r);
@@ -370,7 +369,7 @@ __device__ __forceinline__ void solve_box(const BoxJob &J, const BoxRun &R, BoxS
                 break;
             }
             // the safeguard: from the interpolated guess again, damped
-            w = kDampedStep;
+            damped = true;
             out.damped_from = out.cycles + 1;
             interpolate_level0(false);
             __syncthreads();

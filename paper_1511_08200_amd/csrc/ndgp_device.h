@@ -192,10 +192,10 @@ __device__ __forceinline__ void flush_events(unsigned *counters, unsigned ev) {
     if (ev >> 16) atomicAdd(counters + 1, ev >> 16);
 }
 
-// New value of one cell: the root of its own quadratic with the neighbours
-// held, u + w * du.  w = 1 takes the root itself (w * r is then exactly r);
-// w < 1 damps the step, for the safeguarded iteration of the driver (every
-// branch is damped the same way).
+// New value of one cell: u + w * du towards the root of its own quadratic with
+// the neighbours held.  w > 1 over-relaxes the ordinary step (a cell past its
+// vertex, or with no root, moves to the root or the vertex itself); w < 1 damps
+// every branch, for the safeguarded iteration of the driver.
 __device__ __forceinline__ double relax_cell(const double v[19], double s, double al, double w,
                                              unsigned &events) {
     const Terms t = stencil_terms(v);
@@ -204,11 +204,11 @@ __device__ __forceinline__ double relax_cell(const double v[19], double s, doubl
     const double D = fma(B, B, -18.0 * al * r);
     if (D < 0.0) {
         ++events;
-        return fma(w, B / (18.0 * al), v[0]);
+        return fma(fmin(w, 1.0), B / (18.0 * al), v[0]);
     }
     if (B > 0.0) return fma(w * r, fast_rcp(B + fast_sqrt(D)), v[0]);
     events += kPastVertexEvent;
-    return fma(w, (B - fast_sqrt(D)) / (18.0 * al), v[0]);
+    return fma(fmin(w, 1.0), (B - fast_sqrt(D)) / (18.0 * al), v[0]);
 }
 
 // Coarse levels of a refinement: the ghosts whose correction is taken from

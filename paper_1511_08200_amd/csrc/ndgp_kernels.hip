@@ -311,12 +311,16 @@ k_sweep_fused(const double *__restrict__ pin, double *__restrict__ pout,
                 c0[lo + 2 * HX + 1], c0[lo + 1], c0[lo + 2 * HX], c0[lo],
                 p0[lo + HX + 1], m0[lo + HX + 1], p0[lo + HX], m0[lo + HX],
                 p0[lj + 2 * HX], m0[lj + 2 * HX], p0[lj], m0[lj]};
-            if constexpr (PER) {
-                rz[lj + HX] = relax_cell(v, src[e], al, w, fb);
-            } else {
-                const int gx = x0 - 2 + 2 * (red_jj[e] + 1 - p) + p, gy = y0 - 2 + red_rr[e];
-                rz[lj + HX] = ghost(gx, gy, z) || hold[e] ? v[0] : relax_cell(v, src[e], al, w, fb);
-            }
+            const int gx = x0 - 2 + 2 * (red_jj[e] + 1 - p) + p, gy = y0 - 2 + red_rr[e];
+            unsigned ev = 0;
+            if constexpr (PER)
+                rz[lj + HX] = relax_cell(v, src[e], al, w, ev);
+            else
+                rz[lj + HX] = ghost(gx, gy, z) || hold[e] ? v[0] : relax_cell(v, src[e], al, w, ev);
+            // a halo cell's events are counted by the workgroup that owns it
+            if (ev && (unsigned)(gx - x0) < (unsigned)TX && (unsigned)(gy - y0) < (unsigned)TY &&
+                (unsigned)(z - z0) < (unsigned)TZ)
+                fb += ev;
         }
     };
 
@@ -1122,7 +1126,7 @@ k_bottom(double *__restrict__ phi, const double *__restrict__ s, int lg0, Bottom
         const Ix<true> ix = {n, lg, n + 2};
         double *ph = PHI + off(q);
         const double *sr = SRC + off(q);
-        const double al = alpha(q);
+        const double al = alpha(q), w = q == nb - 1 ? bl.omega_c : bl.omega;
         const int ncol = (n * n * n) >> 1; // cells of one colour
         // new value of the t-th cell of colour col, or at = -1 past the last
         auto cell = [&](int t, int col, double &val, int &at) {
@@ -1134,7 +1138,7 @@ k_bottom(double *__restrict__ phi, const double *__restrict__ s, int lg0, Bottom
             const int i = 2 * m + ((col ^ j ^ k) & 1);
             double v[19];
             gather(ph, ix, i, j, k, v);
-            val = relax_cell(v, sr[((k << lg) + j) * n + i], al, bl.omega, fb);
+            val = relax_cell(v, sr[((k << lg) + j) * n + i], al, w, fb);
             at = ix(i, j, k);
         };
         for (int sw = 0; sw < sweeps; ++sw)
@@ -1288,7 +1292,7 @@ k_bottom_dir(BottomDirLevels bl, int nu1, int nu2, int csweeps, unsigned *__rest
         const double *hh = HAT + poff(q);
         const double *sr = SRC + coff(q);
         const unsigned char *mk = MSK + coff(q);
-        const double al = alpha(q);
+        const double al = alpha(q), w = q == nb - 1 ? bl.omega_c : bl.omega;
         const int ncol = (n * n * n) >> 1; // cells of one colour
         for (int sw = 0; sw < sweeps; ++sw)
             for (int col = 0; col < 2; ++col) {
@@ -1308,7 +1312,7 @@ k_bottom_dir(BottomDirLevels bl, int nu1, int nu2, int csweeps, unsigned *__rest
                         if (mk[nat]) { // a held cell keeps its value (and its ghosts)
                             double g[19];
                             gather(ph, ix, i, j, k, g);
-                            v[c] = relax_cell(g, sr[nat], al, bl.omega, fb);
+                            v[c] = relax_cell(g, sr[nat], al, w, fb);
                             cell[c] = nat;
                         }
                     }
@@ -1890,6 +1894,7 @@ void launch_bottom(const Level *H, int l, int nl, int nu1, int nu2, int csweeps,
     bl.levels = nl - l;
     for (int q = 0; q < bl.levels; ++q) bl.alpha[q] = H[l + q].alpha;
     bl.omega = H[l].omega;
+    bl.omega_c = H[nl - 1].omega;
     k_bottom<<<1, kBottomThreads, 0, st>>>(H[l].phi, H[l].s, H[l].lg, bl, nu1, nu2, csweeps,
                                            fallbacks);
 }
@@ -1907,6 +1912,7 @@ void launch_bottom_dir(const Level *H, int l, int nl, int nu1, int nu2, int cswe
     bl.levels = nl - l;
     bl.lg0 = H[l].lg;
     bl.omega = H[l].omega;
+    bl.omega_c = H[nl - 1].omega;
     bl.phi0 = H[l].phi;
     bl.s0 = H[l].s;
     for (int q = 0; q < bl.levels; ++q) {

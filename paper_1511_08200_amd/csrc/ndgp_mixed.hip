@@ -78,11 +78,11 @@ __device__ __forceinline__ float relax_corr_cell(const float vp[19], const float
     const double D = fma(B, B, -18.0 * ad * rT);
     if (D < 0.0) {
         ++fallbacks;
-        return (float)fma(w, B / (18.0 * ad), (double)ve[0]);
+        return (float)fma(fmin(w, 1.0), B / (18.0 * ad), (double)ve[0]);
     }
     if (B > 0.0) return (float)fma(w * rT, fast_rcp(B + fast_sqrt(D)), (double)ve[0]);
     fallbacks += kPastVertexEvent;
-    return (float)fma(w, (B - fast_sqrt(D)) / (18.0 * ad), (double)ve[0]);
+    return (float)fma(fmin(w, 1.0), (B - fast_sqrt(D)) / (18.0 * ad), (double)ve[0]);
 }
 
 using IxP = Ix<true>;
@@ -482,7 +482,7 @@ k_corr_sweep_fused(const float *__restrict__ ein, float *__restrict__ eout,
             out[e] = *plane_at(rp, (unsigned)(((gy & m) << lg) | (gx & m)));
         }
     };
-    auto red_plane = [&](auto pl, const float src[2]) {
+    auto red_plane = [&](int z, auto pl, const float src[2]) {
         constexpr int d = decltype(pl)::d;
         const float *pm0 = F[ring_slot(d - 1, 6)][0][0], *pm1 = F[ring_slot(d - 1, 6)][1][0];
         const float *pc0 = F[ring_slot(d, 6)][0][0], *pc1 = F[ring_slot(d, 6)][1][0];
@@ -511,7 +511,13 @@ k_corr_sweep_fused(const float *__restrict__ ein, float *__restrict__ eout,
                 c0[lo + 2 * HX + 1], c0[lo + 1], c0[lo + 2 * HX], c0[lo],
                 p0[lo + HX + 1], m0[lo + HX + 1], p0[lo + HX], m0[lo + HX],
                 p0[lj + 2 * HX], m0[lj + 2 * HX], p0[lj], m0[lj]};
-            rz[lj + HX] = relax_corr_cell(vp, ve, src[e], al, w, fb);
+            unsigned ev = 0;
+            rz[lj + HX] = relax_corr_cell(vp, ve, src[e], al, w, ev);
+            // a halo cell's events are counted by the workgroup that owns it
+            const int gx = x0 - 2 + 2 * (red_jj[e] + 1 - p) + p, gy = y0 - 2 + red_rr[e];
+            if (ev && (unsigned)(gx - x0) < (unsigned)TX && (unsigned)(gy - y0) < (unsigned)TY &&
+                (unsigned)(z - z0) < (unsigned)TZ)
+                fb += ev;
         }
     };
 
@@ -578,7 +584,7 @@ k_corr_sweep_fused(const float *__restrict__ ein, float *__restrict__ eout,
     fetch(z0 + 1);
     if constexpr (PRO) e_load(c0 + 1);
     __syncthreads();
-    red_plane(Plane<-1>{}, ra);
+    red_plane(z0 - 1, Plane<-1>{}, ra);
     __syncthreads(); // red(z0-1) has read the red slot that plane z0+1 takes
     if constexpr (PRO) {
         e_store(Plane<1>{}); // the slot of coarse plane c0-2, last used by plane z0-2
@@ -588,7 +594,7 @@ k_corr_sweep_fused(const float *__restrict__ ein, float *__restrict__ eout,
     red_sources(z0, Plane<0>{}, ra);
     fetch(z0 + 2);
     __syncthreads();
-    red_plane(Plane<0>{}, ra);
+    red_plane(z0, Plane<0>{}, ra);
     __syncthreads();
     red_sources(z0 + 1, Plane<1>{}, ra);
     ba = black_source(z0, Plane<0>{});
@@ -606,7 +612,7 @@ k_corr_sweep_fused(const float *__restrict__ ein, float *__restrict__ eout,
         fetch(k + 3);
         __syncthreads();
         if constexpr (PRO && !(d & 1)) e_store(Plane<d / 2 + 2>{});
-        red_plane(Plane<d + 1>{}, use_r);
+        red_plane(k + 1, Plane<d + 1>{}, use_r);
         __syncthreads();
         black_and_store(k, Plane<d>{}, use_b);
     };

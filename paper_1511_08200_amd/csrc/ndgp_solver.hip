@@ -426,8 +426,10 @@ ndgp_status verdict(const CycleMonitor &m) {
     }
 }
 
-inline void set_step(Level *H, Level32 *H32, int nl, double w) {
+// the step factors of a hierarchy: over-relaxed, or damped for the safeguard
+inline void set_step(Level *H, Level32 *H32, int nl, bool damped) {
     for (int l = 0; l < nl; ++l) {
+        const double w = step_factor(damped, l == nl - 1);
         H[l].omega = w;
         if (H32) H32[l].omega = w;
     }
@@ -533,15 +535,17 @@ struct Runner {
     void vcycle(Level *H, int nl, int l) {
         Level &L = H[l];
         if (l == nl - 1) {
-            launch_coarsest(L, kCoarsestSweeps, P.fallbacks, st);
+            launch_coarsest(L, coarsest_sweeps(L.omega == kDampedStep), P.fallbacks, st);
             return;
         }
         if (!(P.c.flags & NDGP_TWO_PASS) && bottom_ok(H, l, nl)) {
-            launch_bottom(H, l, nl, P.c.nu1, P.c.nu2, kCoarsestSweeps, P.fallbacks, st);
+            launch_bottom(H, l, nl, P.c.nu1, P.c.nu2, coarsest_sweeps(L.omega == kDampedStep),
+                          P.fallbacks, st);
             return;
         }
         if (!(P.c.flags & NDGP_TWO_PASS) && bottom_dir_ok(H, l, nl)) {
-            launch_bottom_dir(H, l, nl, P.c.nu1, P.c.nu2, kCoarsestSweeps, P.fallbacks, st);
+            launch_bottom_dir(H, l, nl, P.c.nu1, P.c.nu2, coarsest_sweeps(L.omega == kDampedStep),
+                              P.fallbacks, st);
             return;
         }
         smooth(L, P.c.nu1);
@@ -561,7 +565,8 @@ struct Runner {
         P.phi32_fresh = false;
         for (int l = 1; l < nl; ++l) launch_restrict_source(H[l - 1], H[l], st);
         launch_fill(H[nl - 1].phi, H[nl - 1].slots(), 0.0, st);
-        launch_coarsest(H[nl - 1], kCoarsestSweeps, P.fallbacks, st);
+        launch_coarsest(H[nl - 1], coarsest_sweeps(H[nl - 1].omega == kDampedStep), P.fallbacks,
+                        st);
         for (int l = nl - 2; l >= 0; --l) {
             launch_prolong_full(H[l], H[l + 1], st);
             if (l > 0) vcycle(H, nl, l);
@@ -610,7 +615,7 @@ struct Runner {
     void corr_vcycle(Level32 *H, int nl, int l, bool from_zero = false) {
         Level32 &L = H[l];
         if (l == nl - 1) {
-            launch_corr_coarsest(L, kCoarsestSweeps, P.fallbacks, st);
+            launch_corr_coarsest(L, coarsest_sweeps(L.omega == kDampedStep), P.fallbacks, st);
             return;
         }
         corr_smooth(L, P.c.nu1, nullptr, from_zero);
@@ -638,7 +643,7 @@ struct Runner {
                             double &rel, double *hist, int *hist_len, bool *restart,
                             double rr0 = -1.0) {
         CycleMonitor m{P.c.tol, P.c.maxc};
-        m.damped = H[0].omega != 1.0;
+        m.damped = H[0].omega == kDampedStep;
         m.start(std::sqrt((rr0 >= 0.0 ? rr0 : residual_to32(H[0], H32[0].r)) / snorm2));
         rel = m.rel;
         while (outer < m.maxc && !m.converged()) {
@@ -666,7 +671,7 @@ struct Runner {
     ndgp_status drive(Level *H, int nl, double snorm2, int &cycles, double &rel, double *hist,
                       int *hist_len, bool *restart, double rr0 = -1.0) {
         CycleMonitor m{P.c.tol, P.c.maxc};
-        m.damped = H[0].omega != 1.0;
+        m.damped = H[0].omega == kDampedStep;
         m.start(std::sqrt((rr0 >= 0.0 ? rr0 : residual_sumsq(H[0])) / snorm2));
         rel = m.rel;
         while (cycles < m.maxc && !m.converged()) {
@@ -729,13 +734,11 @@ PatchOutcome relax_patch(Runner &run, Level *H, int nlev, const double *parent, 
     }
     if (sn2 == 0.0) sn2 = std::max(run.residual_sumsq(H[0]), 1e-300);
     bool restart = false;
-    if (c.flags & NDGP_DAMPED) {
-        set_step(H, nullptr, nlev, kDampedStep);
-        out.damped_from = 1;
-    }
+    set_step(H, nullptr, nlev, (c.flags & NDGP_DAMPED) != 0);
+    if (c.flags & NDGP_DAMPED) out.damped_from = 1;
     out.status = run.drive(H, nlev, sn2, out.cycles, out.rel, nullptr, nullptr, &restart);
     if (restart) { // the safeguard: from the interpolated guess again, damped
-        set_step(H, nullptr, nlev, kDampedStep);
+        set_step(H, nullptr, nlev, true);
         out.damped_from = out.cycles + 1;
         launch_interpolate(parent, npar, parent_periodic, b0, H[0].phi, false, st);
         out.status = run.drive(H, nlev, sn2, out.cycles, out.rel, nullptr, nullptr, nullptr);
@@ -806,10 +809,9 @@ ndgp_status solve_impl(const ndgp_grid *grid, const ndgp_params *params,
     launch_source(delta[0], cells0, P.scal + 0, 1.0 / (double)cells0, c.fsrc * c.h * c.h,
                   P.base[0].s, st);
     run.enqueue_sum(P.base[0].s, cells0, true, 1);
-    if (c.flags & NDGP_DAMPED) { // the damped step from the start
-        set_step(P.base, c.prec == NDGP_PREC_MIXED ? P.base32 : nullptr, c.nl, kDampedStep);
-        R.damped_from[0] = 1;
-    }
+    set_step(P.base, c.prec == NDGP_PREC_MIXED ? P.base32 : nullptr, c.nl,
+             (c.flags & NDGP_DAMPED) != 0);
+    if (c.flags & NDGP_DAMPED) R.damped_from[0] = 1; // the damped step from the start
     if (!(c.flags & NDGP_WARM_START)) run.nested_start(P.base, c.nl);
     run.enqueue_residual(P.base, P.base32);
     run.read_scalars(P.scal, 3);
@@ -838,7 +840,7 @@ ndgp_status solve_impl(const ndgp_grid *grid, const ndgp_params *params,
             timer.on = false;
             if (!restart) break;
             // the safeguard: solve again from the nested start with the damped step
-            set_step(P.base, c.prec == NDGP_PREC_MIXED ? P.base32 : nullptr, c.nl, kDampedStep);
+            set_step(P.base, c.prec == NDGP_PREC_MIXED ? P.base32 : nullptr, c.nl, true);
             R.damped_from[0] = R.cycles[0] + 1;
         }
         R.rel_res[0] = rel;
@@ -1155,8 +1157,8 @@ ndgp_status solve_amr_impl(const ndgp_grid *grid, const ndgp_params *params,
     // Level by level of the tree (a box after its parent): relaxed boxes of at
     // most kBoxBatchMaxN cells per side all in one launch, one workgroup each
     // (the same bits as relax_patch); the others one after the other.
-    const BoxRun brun{P.scal + 0, 1.0 / (double)cells0, c.nu1, c.nu2, kCoarsestSweeps, c.maxc,
-                      c.tol, (c.flags & NDGP_DAMPED) ? 1 : 0, P.fallbacks};
+    const BoxRun brun{P.scal + 0, 1.0 / (double)cells0, c.nu1, c.nu2, c.maxc, c.tol,
+                      (c.flags & NDGP_DAMPED) ? 1 : 0, P.fallbacks};
     std::vector<BoxJob> jobs;
     std::vector<int> job_box;
     jobs.reserve((size_t)nbatch); // no reallocation: copies read from these elements
@@ -1681,11 +1683,9 @@ ndgp_status plan_create_impl(const ndgp_grid *grid, const ndgp_params *params,
         launch_source(delta[0], cells0, pl->P.scal + 0, 1.0 / (double)cells0, c.fsrc * c.h * c.h,
                       pl->P.base[0].s, st);
         run.enqueue_sum(pl->P.base[0].s, cells0, true, 1);
-        if (c.flags & NDGP_DAMPED) {
-            set_step(pl->P.base, c.prec == NDGP_PREC_MIXED ? pl->P.base32 : nullptr, c.nl,
-                     kDampedStep);
-            pl->R.damped_from[0] = 1;
-        }
+        set_step(pl->P.base, c.prec == NDGP_PREC_MIXED ? pl->P.base32 : nullptr, c.nl,
+                 (c.flags & NDGP_DAMPED) != 0);
+        if (c.flags & NDGP_DAMPED) pl->R.damped_from[0] = 1;
         if (!(c.flags & NDGP_WARM_START)) run.nested_start(pl->P.base, c.nl);
         run.enqueue_residual(pl->P.base, pl->P.base32);
         HIP_TRY(hipMemcpyAsync(pl->slot, pl->P.scal, 3 * sizeof(double), hipMemcpyDeviceToHost,
@@ -1773,8 +1773,7 @@ ndgp_status plan_poll_impl(ndgp_plan *pl, int32_t *done, ndgp_report *rep) {
             pl->R.hist_len = cyc;
         }
         if (pl->mon.record(r)) { // the safeguard: from the nested start again, damped
-            set_step(pl->P.base, c.prec == NDGP_PREC_MIXED ? pl->P.base32 : nullptr, c.nl,
-                     kDampedStep);
+            set_step(pl->P.base, c.prec == NDGP_PREC_MIXED ? pl->P.base32 : nullptr, c.nl, true);
             pl->R.damped_from[0] = cyc + 1;
             pl->restarting = true;
             Runner run = plan_runner(pl);

@@ -83,6 +83,31 @@ def test_periodic_solution_matches_oracle(n, box, sigma, tophats, rc, seed):
     assert rel(phig, phio) <= PHI_TOL
 
 
+@pytest.mark.parametrize("n,levels,nu1,nu2,rc,precision", [
+    (8, 3, 2, 2, 1.0, ndgp.PREC_FP64),   # coarsest 2^3 cells
+    (16, 3, 2, 1, 5.0, ndgp.PREC_FP64),  # coarsest 4^3 cells
+    (32, 0, 1, 1, 0.0, ndgp.PREC_FP64),
+    (32, 0, 3, 3, 5.0, ndgp.PREC_FP64),
+    (32, 0, 2, 2, 5.0, ndgp.PREC_MIXED),
+])
+def test_over_relaxed_cycles(n, levels, nu1, nu2, rc, precision):
+    """The over-relaxed step reaches the oracle's solution for every coarsest
+    size and sweep count, never restarts, and needs no more cycles than the
+    damped step."""
+    say(f"over-relaxed n={n} levels={levels} nu={nu1},{nu2} rc={rc} precision={precision}")
+    f = synth.make_field(n, 2.0, 17, n_tophats=n // 8)
+    h = ndgp.cell_size(float(n), n)
+    phio, _ = oracle_periodic(f.delta, h, rc)
+    mixed = precision == ndgp.PREC_MIXED
+    kw = dict(rc=rc, n_levels=levels, nu1=nu1, nu2=nu2, precision=precision, max_cycles=200)
+    (phig,), rep = gpu_solve([f.delta], ndgp.Grid(n=n, h=h), tol=1e-12 if mixed else 0.0, **kw)
+    assert rep.status == 0 and not any(rep.damped_from)
+    assert rel(phig, phio) <= (1e-8 if mixed else PHI_TOL)
+    _, fast = gpu_solve([f.delta], ndgp.Grid(n=n, h=h), tol=1e-10, **kw)
+    _, slow = gpu_solve([f.delta], ndgp.Grid(n=n, h=h), tol=1e-10, damped=True, **kw)
+    assert fast.status == 0 and slow.status == 0 and fast.cycles[0] <= slow.cycles[0]
+
+
 def test_tolerance_stop_and_history():
     n = 32
     f = synth.make_field(n, 1.0, 1512)
