@@ -385,7 +385,11 @@ ndgp_status ndgp_geff_stats(const ndgp_grid *grid, const double *const phi[1 + N
  *                     64-bit fixed-point numbers (2^-36 of a particle), so the
  *                     result is the same bits on every run.  1 <= N <=
  *                     NDGP_CIC_MAX_PARTICLES.  Workspace:
- *                     ndgp_cic_workspace_bytes(grid).  Enqueues only.
+ *                     ndgp_cic_workspace_bytes(grid): 8 bytes per cell of
+ *                     every level, and scratch to sort the particles by tile
+ *                     (a workspace without room for that scratch is accepted;
+ *                     the deposit then is slower, with the same bits).
+ *                     Enqueues only.
  * ndgp_cic_force      out (3 * N, x then y then z) = cloud-in-cell interpolation
  *                     of force[l] (3 * cells(l), as ndgp_force or
  *                     ndgp_total_force write it) from the finest level whose

@@ -323,12 +323,37 @@ void launch_geff_level(const double *phi, const double *psi, int n, bool periodi
                        int n_edges, double *partials, unsigned long long *hist, double *out,
                        hipStream_t st);
 
+// Scratch of the binned deposit: up to `chunk` particles are sorted by the tile
+// that holds their lower cell before they are added.  sorted == null: none (every
+// particle adds its weights straight into the accumulators).
+struct CicSegment {
+    unsigned bin, first, count, whole; // whole: the tile's only segment
+};
+constexpr int kCicBlocks = 1024; // workgroups of the sort, at most
+struct CicScratch {
+    double *sorted = nullptr;      // 3 * chunk: x, y, z of one particle after the other
+    unsigned *table = nullptr;     // kCicBlocks * bins: a workgroup's place in each tile
+    unsigned *base = nullptr;      // bins: first particle of each tile
+    CicSegment *segments = nullptr;
+    unsigned *n_segments = nullptr;
+    size_t chunk = 0;
+};
+// tiles of a level of m cells per side (0: the level is not binned), the segments
+// a chunk can give, and the chunk for a domain of n cells per side
+int cic_bins(int m);
+size_t cic_segments(int m, size_t chunk);
+size_t cic_chunk(int n);
+// 64-bit words of a level's accumulators and tile counters
+size_t cic_acc_words(int m);
+void launch_zero_words(unsigned long long *a, size_t count, hipStream_t st);
 // Cloud-in-cell deposit of np particles (pos: x, y, z arrays of np doubles
 // each, box units) onto one level: m^3 cells of 2^-q domain cells with lower
 // corner `corner` (domain cells); q = 0 is the periodic domain (m = n).
-// acc: m^3 fixed-point accumulators; delta = count / mean - 1.
+// acc: cic_acc_words(m) words (m^3 fixed-point accumulators first; only those
+// without scratch), zero on entry; delta = count / mean - 1.
 void launch_cic_deposit(const double *pos, long long np, int n, const double corner[3], int q,
-                        int m, unsigned long long *acc, double *delta, hipStream_t st);
+                        int m, unsigned long long *acc, double *delta, const CicScratch &scr,
+                        hipStream_t st);
 // flags = (delta + 1) mean > n_ref; partials[0..kReduceBlocks) = per-block
 // counts of flagged cells.
 void launch_refine_flags(const double *delta, size_t cells, double mean, double n_ref,

@@ -1500,14 +1500,37 @@ void level_corners(const Cfg &c, double corner[][3]) {
             corner[q + 1][a] = corner[q][a] + std::ldexp((double)c.po[q][a], -q);
 }
 
-size_t cic_bytes(const Cfg &c) {
-    Carver cv{nullptr};
+// The deposit's workspace: every level's accumulators, then the scratch of the
+// particle sort (one level at a time, so sized for the level that needs most).
+// A workspace that holds the accumulators alone (`plain`) is accepted: the
+// deposit then sends every particle's atomics to memory.
+size_t carve_cic(const Cfg &c, char *base, bool plain, unsigned long long **acc,
+                 CicScratch *scr) {
+    Carver cv{base};
+    size_t bins = 0, segments = 0;
+    const size_t chunk = cic_chunk(c.n);
     for (int l = 0; l <= c.np; ++l) {
-        const size_t m = (size_t)c.nlev(l);
-        cv.take<unsigned long long>(m * m * m);
+        const int m = c.nlev(l);
+        unsigned long long *a = cv.take<unsigned long long>(plain ? (size_t)m * m * m
+                                                                  : cic_acc_words(m));
+        if (acc) acc[l] = a;
+        bins = std::max(bins, (size_t)cic_bins(m));
+        segments = std::max(segments, cic_segments(m, chunk));
+    }
+    if (!plain && bins > 0) {
+        CicScratch s;
+        s.chunk = chunk;
+        s.sorted = cv.take<double>(3 * chunk);
+        s.table = cv.take<unsigned>(kCicBlocks * bins);
+        s.base = cv.take<unsigned>(bins);
+        s.segments = cv.take<CicSegment>(segments);
+        s.n_segments = cv.take<unsigned>(1);
+        if (scr) *scr = s;
     }
     return cv.off + 256;
 }
+
+size_t cic_bytes(const Cfg &c) { return carve_cic(c, nullptr, false, nullptr, nullptr); }
 
 ndgp_status cic_density_impl(const ndgp_grid *grid, const double *pos, int64_t np,
                              double *const delta[], void *ws, size_t ws_bytes, hipStream_t st) {
@@ -1519,17 +1542,23 @@ ndgp_status cic_density_impl(const ndgp_grid *grid, const double *pos, int64_t n
         return fail(NDGP_EINVAL, "n_particles must be in [1, NDGP_CIC_MAX_PARTICLES]");
     for (int l = 0; l <= c.np; ++l)
         if (!delta[l]) return fail(NDGP_EINVAL, "delta of every level must not be NULL");
-    if (!ws || ws_bytes < cic_bytes(c))
+    const bool plain = ws_bytes < cic_bytes(c);
+    if (!ws || ws_bytes < carve_cic(c, nullptr, true, nullptr, nullptr))
         return fail(NDGP_ENOMEM, "workspace smaller than ndgp_cic_workspace_bytes() = " +
                                      std::to_string(cic_bytes(c)));
     double corner[1 + NDGP_MAX_PATCHES][3];
     level_corners(c, corner);
-    Carver cv{aligned_base(ws)};
-    for (int l = 0; l <= c.np; ++l) {
-        const int m = c.nlev(l);
-        unsigned long long *acc = cv.take<unsigned long long>((size_t)m * m * m);
-        launch_cic_deposit(pos, (long long)np, c.n, corner[l], l, m, acc, delta[l], st);
-    }
+    unsigned long long *acc[1 + NDGP_MAX_PATCHES];
+    CicScratch scr;
+    carve_cic(c, aligned_base(ws), plain, acc, &scr);
+    // the levels' accumulators lie one after the other: cleared together
+    const size_t last = (size_t)c.nlev(c.np);
+    launch_zero_words(acc[0], (size_t)(acc[c.np] - acc[0]) +
+                                  (plain ? last * last * last : cic_acc_words(c.nlev(c.np))),
+                      st);
+    for (int l = 0; l <= c.np; ++l)
+        launch_cic_deposit(pos, (long long)np, c.n, corner[l], l, c.nlev(l), acc[l], delta[l],
+                           scr, st);
     HIP_TRY(hipGetLastError());
     return NDGP_OK;
 }

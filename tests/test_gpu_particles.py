@@ -88,6 +88,40 @@ def test_cic_full_size_sampled():
     assert abs(got.mean()) <= 1e-10
 
 
+@pytest.mark.parametrize("n,m,count,where", [
+    (8, 0, 70001, "uniform"),            # one tile, wrapping onto itself
+    (32, 32, 49664, "field"),            # the fewest particles that are sorted
+    (32, 64, (1 << 20) + 4097, "field"),  # two chunks; a patch as wide as the domain
+    (64, 32, 300001, "cell"),            # every particle in one cell: several segments
+    (128, 64, 400003, "ordered"),        # 16^3 tiles, particles in cell order
+    (256, 128, 1000003, "field"),        # 32 x 32 x 16 tiles
+    (256, 0, 311296, "cell"),
+    (512, 0, 2146305, "uniform"),        # the most tiles
+])
+def test_binned_deposit_equals_direct_atomics(n, m, count, where):
+    """The deposit through sorted tiles gives the bits of the direct atomics
+    (the path a workspace with room for the accumulators alone takes)."""
+    say(f"binned deposit n={n} patch={m} particles={count} {where}")
+    rng = np.random.default_rng(count)
+    if where == "uniform":
+        pos = rng.random((3, count))
+    elif where == "cell":  # on both sides of a cell centre next to the periodic edge
+        pos = (np.array([[0.3], [n - 1 + 0.2], [5.1]]) + 0.6 * rng.random((3, count))) / n
+    else:
+        f = synth.make_field(min(n, 64), 1.5, 4)
+        pos = synth.make_particles(f, count, 9, cell_order=where == "ordered")
+    patches = [ndgp.Patch(m, (n - m // 4, -3, n // 2))] if m else []  # wraps the domain
+    grid = ndgp.Grid(n=n, h=ndgp.cell_size(float(n), n), patches=patches)
+    p = dev(np.minimum(pos, np.nextafter(1.0, 0.0)))
+    plain = 8 * (n**3 + m**3) + 4096  # room for guard bands
+    direct = ndgp.cic_density(grid, p, ws=torch.empty(plain, dtype=torch.uint8, device="cuda"))
+    got = ndgp.cic_density(grid, p)
+    torch.cuda.synchronize()
+    for a, b in zip(got, direct):
+        assert torch.equal(a, b)
+    assert abs(float(got[0].mean())) <= 1e-10
+
+
 def test_cic_rejects_bad_arguments():
     grid = ndgp.Grid(n=32, h=ndgp.cell_size(32.0, 32))
     with pytest.raises(ValueError):
