@@ -267,6 +267,27 @@ struct BottomDirLevels {
 bool bottom_dir_ok(const Level *H, int l, int nl);
 void launch_bottom_dir(const Level *H, int l, int nl, int nu1, int nu2, int csweeps,
                        unsigned *fallbacks, hipStream_t st);
+// `sweeps` (1 or 2) red-black sweeps of a periodic level of 16^3 to 64^3 cells in
+// one launch (ndgp_tiles.hip), pin -> pout; pro: starting from pin + P(phi_c -
+// hat_c); rest: followed by the FAS restriction and coarse source into hat_out,
+// s_out and phi_out.  Bit for bit the per-level launches.
+template <class T>
+struct TileArgs {
+    const T *pin;
+    T *pout;
+    const T *base; // the field that the correction e is about (FP32 only)
+    const T *s;
+    int lg;
+    T al;
+    double w;
+    unsigned *events;
+    int from_zero;            // the field is zero and not read (FP32 only)
+    const T *phi_c, *hat_c;   // pro
+    T *hat_out, *s_out, *phi_out; // rest
+    const T *base_c;
+    T al_c;
+};
+void launch_tile(const TileArgs<double> &a, int sweeps, bool pro, bool rest, hipStream_t st);
 // s = f * (delta - sum[0] * inv_count_mean)     (sum: device scalar)
 void launch_source(const double *delta, size_t count, const double *sum, double inv_count_mean,
                    double f, double *s, hipStream_t st);

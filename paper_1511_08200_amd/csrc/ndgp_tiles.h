@@ -1,0 +1,31 @@
+// ndgp_tiles.h -- what the one-launch levels (ndgp_tiles.hip) need to know of the
+// field they relax.  Not part of the public ABI.
+#pragma once
+
+#include "ndgp_device.h"
+
+namespace ndgp {
+
+template <int V>
+struct Int {
+    static constexpr int value = V;
+};
+
+// the FP64 field itself
+struct TileField {
+    using T = double;
+    using Pair = double2;
+    static constexpr bool two = false;
+    __device__ __forceinline__ static double fma_(double a, double b, double c) {
+        return fma(a, b, c);
+    }
+    __device__ __forceinline__ static double relax(const double v[19], const double *, double s,
+                                                   double al, double w, unsigned &ev) {
+        return dev::relax_cell(v, s, al, w, ev);
+    }
+    __device__ __forceinline__ static double apply(const double v[19], const double *, double al) {
+        return dev::apply_L(dev::stencil_terms(v), al);
+    }
+};
+
+} // namespace ndgp

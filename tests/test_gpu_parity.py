@@ -184,6 +184,33 @@ def test_scale_law_bitwise_and_determinism():
     assert np.array_equal(p3, p1)
 
 
+@pytest.mark.parametrize("precision", [ndgp.PREC_FP64, ndgp.PREC_MIXED])
+@pytest.mark.parametrize("n,nu1,nu2", [(32, 1, 1), (32, 1, 2), (32, 2, 2), (32, 4, 3), (64, 2, 1),
+                                       (64, 1, 4), (64, 3, 3), (128, 2, 2)])
+def test_tile_levels_bitwise_equal_per_level_launches(n, nu1, nu2, precision):
+    """The 32^3 and 64^3 levels in one launch per descent and ascent, for every
+    split of the sweeps into launches: the same bits and event counts as one
+    launch per colour and transfer, from a guess whose cells lie past their
+    vertex in places."""
+    say(f"tile levels n={n} nu={nu1},{nu2} precision={precision}")
+    f = synth.make_field(n, 2.0, 37, n_tophats=n // 8)
+    grid = ndgp.Grid(n=n, h=ndgp.cell_size(float(n), n))
+    d = dev(f.delta)
+    guess = dev(1.6e-8 * np.random.default_rng(5).standard_normal((n, n, n)))
+    out = []
+    for two_pass in (False, True):
+        params = ndgp.Params(rc=5.0, tol=1e-13, max_cycles=4, nu1=nu1, nu2=nu2, warm_start=True,
+                             precision=precision, two_pass=two_pass)
+        out.append(ndgp.solve(grid, params, [d], phi=[guess.clone()], check=False))
+    (a, ra), (b, rb) = out
+    torch.cuda.synchronize()
+    say(f"  holds={ra.holds} fallbacks={ra.fallbacks} hist={ra.history}")
+    assert ra.holds > 0
+    assert ra.cycles == rb.cycles and ra.history == rb.history
+    assert ra.holds == rb.holds and ra.fallbacks == rb.fallbacks
+    assert torch.equal(a[0], b[0])
+
+
 @pytest.mark.parametrize("n,levels", [(16, 0), (32, 0), (64, 0), (64, 5), (64, 6), (128, 0),
                                       (256, 0)])
 def test_fused_kernels_bitwise_equal_per_level_launches(n, levels):
