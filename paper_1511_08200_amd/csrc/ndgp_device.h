@@ -324,6 +324,7 @@ __device__ __forceinline__ int xcd_local_id(int lin, int total) {
 
 // ------------------------------------------------------------------------
 // deterministic block sum (kBlock = 256 threads = 4 waves of 64)
+// and, over the blocks, sum_tail
 
 __device__ __forceinline__ double block_sum(double v) {
 #pragma unroll
@@ -334,6 +335,42 @@ __device__ __forceinline__ double block_sum(double v) {
     double r = 0.0;
     if (threadIdx.x == 0) r = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
     return r;
+}
+
+// The end of a reduction over the blocks of a launch: every block leaves its sum
+// (thread 0's b) in partials; with tail.counter the last block to do so adds
+// them all up, in k_reduce_final's order, so that the sum needs no launch of its
+// own (5 us), and writes it to tail.out and, where the host waits for it, to
+// tail.host (pinned memory: no copy).  Partials and counter are only touched by
+// read-modify-write atomics, which complete at the memory side where all XCDs
+// see them; a block's partial is complete (its old value has come back) before
+// it counts itself.  The last block leaves the counter at zero.
+__device__ __forceinline__ void sum_tail(double b, double *__restrict__ partials,
+                                         const SumTail &tail) {
+    if (!tail.counter) {
+        if (threadIdx.x == 0) partials[blockIdx.x] = b;
+        return;
+    }
+    auto *bits = reinterpret_cast<unsigned long long *>(partials);
+    __shared__ bool last;
+    if (threadIdx.x == 0) {
+        const unsigned long long old =
+            atomicExch(&bits[blockIdx.x], (unsigned long long)__double_as_longlong(b));
+        asm volatile("" ::"v"(old) : "memory");
+        last = atomicAdd(tail.counter, 1u) == gridDim.x - 1;
+    }
+    __syncthreads();
+    if (!last) return;
+    double acc = 0.0;
+    for (unsigned q = threadIdx.x; q < gridDim.x; q += kBlock)
+        acc += __longlong_as_double((long long)atomicAdd(&bits[q], 0ull));
+    const double total = block_sum(acc);
+    if (threadIdx.x == 0) {
+        atomicExch(tail.counter, 0u);
+        tail.out[0] = total;
+        if (tail.host)
+            __hip_atomic_store(tail.host, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
 }
 
 } // namespace dev

@@ -193,6 +193,23 @@ struct ChildBox {
     int nc;
 };
 
+// Where a reducing launcher puts the sum; without `out` it leaves kReduceBlocks
+// partials for launch_reduce_final.  Up to kTailBlocks blocks the last of them
+// adds the partials up (dev::sum_tail), else a launch of its own does: the blocks'
+// atomics on one counter are served one after the other (512 of them made the
+// 128^3 residual 5 us slower than the launch they saved; 128 at 32^3 save 4 us).
+struct SumTail {
+    unsigned *counter = nullptr; // zero before and after
+    double *out = nullptr;       // device
+    double *host = nullptr;      // pinned, or null
+};
+constexpr unsigned kTailBlocks = 256;
+inline SumTail tail_in_launch(const SumTail &t, unsigned blocks) {
+    return t.counter && blocks <= kTailBlocks ? t : SumTail{};
+}
+// out[0] (and host) = sum of `count` partials, unless the launch has done it
+void launch_sum_tail(const SumTail &t, unsigned blocks, const double *partials, hipStream_t st);
+
 // ---- kernel launchers (ndgp_kernels.hip); all enqueue on `st` ------------
 
 // Red-black half sweep: cells of colour `colour` ((i+j+k) & 1) get the root
@@ -213,14 +230,17 @@ void launch_sweep_fused_prolong(const Level &L, const Level &C, const double *pi
                                 unsigned *fallbacks, hipStream_t st);
 // Per-block partial sums of r^2, r = s - L[phi]; optionally r_out = r * scale.
 void launch_residual_sumsq(const Level &L, double *partials, double *r_out, double r_scale,
-                           hipStream_t st);
+                           hipStream_t st, const SumTail &tail = {});
 // The LDS-tiled residual (periodic, n >= 128: residual_tiled_ok) with r rounded
 // to FP32 into r32 and the partial sums of r^2 (FP64).
 bool residual_tiled_ok(const Level &L);
-void launch_residual_tiled_to32(const Level &L, float *r32, double *partials, hipStream_t st);
+void launch_residual_tiled_to32(const Level &L, float *r32, double *partials, hipStream_t st,
+                                const SumTail &tail);
 // Per-block partial sums of a[i]^2 (squares != 0) or a[i] over count values.
 void launch_partial_sums(const double *a, size_t count, bool squares, double *partials,
-                         hipStream_t st);
+                         hipStream_t st, const SumTail &tail = {});
+// host[0..3) (pinned, 32-bit words) = the event counters
+void launch_publish(const unsigned *counters, unsigned *host, hipStream_t st);
 // out[0] = sum of the kReduceBlocks partials, in a fixed order.
 void launch_reduce_final(const double *partials, double *out, hipStream_t st);
 // out[0..3) = sum r^2, sum s^2 and the relative norm, from sums[1] = sum s^2
@@ -291,6 +311,10 @@ void launch_tile(const TileArgs<double> &a, int sweeps, bool pro, bool rest, hip
 // s = f * (delta - sum[0] * inv_count_mean)     (sum: device scalar)
 void launch_source(const double *delta, size_t count, const double *sum, double inv_count_mean,
                    double f, double *s, hipStream_t st);
+// the same with the sum of s^2 (as launch_partial_sums forms it)
+void launch_source_sumsq(const double *delta, size_t count, const double *sum,
+                         double inv_count_mean, double f, double *s, double *partials,
+                         hipStream_t st, const SumTail &tail);
 // a[i] -= sum[0] / count        (sum: device scalar; removes the mean)
 void launch_shift_by_mean(double *a, size_t count, const double *sum, hipStream_t st);
 // a[i] = v
@@ -422,7 +446,8 @@ struct Level32 {
 
 // r32 = float(s - L[phi]) with FP64 arithmetic, and per-block partials of
 // (s - L[phi])^2.
-void launch_residual_to32(const Level &L, float *r32, double *partials, hipStream_t st);
+void launch_residual_to32(const Level &L, float *r32, double *partials, hipStream_t st,
+                          const SumTail &tail);
 // phi32 = float(phi64)
 void launch_to32(const double *a, float *b, size_t count, hipStream_t st);
 // coarse = mean of the 8 children (FP32 field)

@@ -627,7 +627,7 @@ template <int TX, int TY, class OutT, bool PER = true>
 __global__ void __launch_bounds__(kBlock)
 k_residual_tiled(const double *__restrict__ phi, const double *__restrict__ s, int lg, int tz,
                  double al, double *__restrict__ partials, OutT *__restrict__ r_out,
-                 double r_scale, const unsigned char *__restrict__ mask = nullptr) {
+                 double r_scale, const unsigned char *__restrict__ mask, SumTail tail) {
     constexpr int PX = TX + 2, PY = TY + 2, PLANE = PX * PY;
     constexpr int PRE = (PLANE + kBlock - 1) / kBlock;
     constexpr int CELLS = TX * TY / kBlock; // output cells per thread per plane
@@ -695,15 +695,14 @@ k_residual_tiled(const double *__restrict__ phi, const double *__restrict__ s, i
             if (r_out) r_out[g] = (OutT)(r * r_scale);
         }
     }
-    const double b = block_sum(acc);
-    if (threadIdx.x == 0) partials[blockIdx.x] = b;
+    sum_tail(block_sum(acc), partials, tail);
 }
 
 template <bool PER>
 __global__ void __launch_bounds__(kBlock)
 k_residual_sumsq(const double *__restrict__ phi, const double *__restrict__ s, Ix<PER> ix,
                  double al, double *__restrict__ partials, double *__restrict__ r_out,
-                 double r_scale, const unsigned char *__restrict__ mask) {
+                 double r_scale, const unsigned char *__restrict__ mask, SumTail tail) {
     const int n = ix.n, lg = ix.lg;
     const int total = 1 << (3 * lg);
     double acc = 0.0;
@@ -718,21 +717,19 @@ k_residual_sumsq(const double *__restrict__ phi, const double *__restrict__ s, I
         acc = fma(r, r, acc);
         if (r_out) r_out[c] = r * r_scale;
     }
-    const double b = block_sum(acc);
-    if (threadIdx.x == 0) partials[blockIdx.x] = b;
+    sum_tail(block_sum(acc), partials, tail);
 }
 
 __global__ void __launch_bounds__(kBlock)
 k_partial_sums(const double *__restrict__ a, size_t count, int squares,
-               double *__restrict__ partials) {
+               double *__restrict__ partials, SumTail tail) {
     double acc = 0.0;
     for (size_t c = (size_t)blockIdx.x * kBlock + threadIdx.x; c < count;
          c += (size_t)gridDim.x * kBlock) {
         const double x = a[c];
         acc = squares ? fma(x, x, acc) : acc + x;
     }
-    const double b = block_sum(acc);
-    if (threadIdx.x == 0) partials[blockIdx.x] = b;
+    sum_tail(block_sum(acc), partials, tail);
 }
 
 __global__ void __launch_bounds__(kBlock)
@@ -760,11 +757,15 @@ k_diff_partials(const double *__restrict__ a, const double *__restrict__ b, size
 }
 
 __global__ void __launch_bounds__(kBlock)
-k_reduce_final(const double *__restrict__ partials, double *__restrict__ out) {
+k_reduce_final(const double *__restrict__ partials, int count, double *__restrict__ out,
+               double *__restrict__ host) {
     double acc = 0.0;
-    for (int q = threadIdx.x; q < kReduceBlocks; q += kBlock) acc += partials[q];
+    for (int q = threadIdx.x; q < count; q += kBlock) acc += partials[q];
     const double b = block_sum(acc);
-    if (threadIdx.x == 0) out[0] = b;
+    if (threadIdx.x == 0) {
+        out[0] = b;
+        if (host) __hip_atomic_store(host, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
 }
 
 // out = (sum r^2, sum s^2, relative norm) from sums[1] = sum s^2 and
@@ -1413,6 +1414,28 @@ k_source(const double *__restrict__ delta, size_t count, const double *__restric
     s[t] = f * (delta[t] - mean);
 }
 
+// The same with the sum of s^2 in k_partial_sums' order: s is not read again.
+__global__ void __launch_bounds__(kBlock)
+k_source_sumsq(const double *__restrict__ delta, size_t count, const double *__restrict__ sum,
+               double inv_count_mean, double f, double *__restrict__ s,
+               double *__restrict__ partials, SumTail tail) {
+    const double mean = sum[0] * inv_count_mean;
+    double acc = 0.0;
+    for (size_t c = (size_t)blockIdx.x * kBlock + threadIdx.x; c < count;
+         c += (size_t)gridDim.x * kBlock) {
+        const double x = f * (delta[c] - mean);
+        s[c] = x;
+        acc = fma(x, x, acc);
+    }
+    sum_tail(block_sum(acc), partials, tail);
+}
+
+__global__ void k_publish(const unsigned *__restrict__ counters, unsigned *__restrict__ host) {
+    if (threadIdx.x < 3)
+        __hip_atomic_store(&host[threadIdx.x], counters[threadIdx.x], __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 __global__ void __launch_bounds__(kBlock)
 k_shift_by_mean(double *__restrict__ a, size_t count, const double *__restrict__ sum,
                 double inv_count) {
@@ -1751,47 +1774,72 @@ void launch_sweep_fused_prolong(const Level &L, const Level &C, const double *pi
 
 template <class OutT>
 void residual_tiled(const Level &L, double *partials, OutT *r_out, double r_scale,
-                    hipStream_t st) {
+                    hipStream_t st, const SumTail &tail) {
     constexpr int TX = 64, TY = 16;
     const int tiles = (L.n / TX) * (L.n / TY);
     // z-chunks of 8 planes (4 at 128^3: enough workgroups to fill the chip), at
     // most kReduceBlocks workgroups
     int chunks = L.n >= 256 ? L.n / 8 : L.n / 4;
     while (tiles * chunks > kReduceBlocks) chunks /= 2;
+    const SumTail own = tail_in_launch(tail, (unsigned)(tiles * chunks));
     // blocks beyond the grid contribute zeros to the fixed-size final sum
-    const size_t unused = (size_t)(kReduceBlocks - tiles * chunks);
+    const size_t unused = tail.out ? 0 : (size_t)(kReduceBlocks - tiles * chunks);
     if (unused) k_fill<<<blocks_for(unused), kBlock, 0, st>>>(partials + tiles * chunks, unused, 0.0);
     if (L.periodic)
         k_residual_tiled<TX, TY, OutT, true><<<tiles * chunks, kBlock, 0, st>>>(
-            L.phi, L.s, L.lg, L.n / chunks, L.alpha, partials, r_out, r_scale, nullptr);
+            L.phi, L.s, L.lg, L.n / chunks, L.alpha, partials, r_out, r_scale, nullptr, own);
     else
         k_residual_tiled<TX, TY, OutT, false><<<tiles * chunks, kBlock, 0, st>>>(
-            L.phi, L.s, L.lg, L.n / chunks, L.alpha, partials, r_out, r_scale, L.mask);
+            L.phi, L.s, L.lg, L.n / chunks, L.alpha, partials, r_out, r_scale, L.mask, own);
+    launch_sum_tail(tail, (unsigned)(tiles * chunks), partials, st);
+}
+
+// blocks of a reduction over `count` values: those past the values would only add
+// zeros, and are left out where the launch adds up its own partials
+static unsigned reduce_blocks(size_t count, const SumTail &tail) {
+    return tail.out && blocks_for(count) < (unsigned)kReduceBlocks ? blocks_for(count)
+                                                                   : (unsigned)kReduceBlocks;
+}
+
+void launch_sum_tail(const SumTail &t, unsigned blocks, const double *partials, hipStream_t st) {
+    if (t.out && !tail_in_launch(t, blocks).counter)
+        k_reduce_final<<<1, kBlock, 0, st>>>(partials, (int)blocks, t.out, t.host);
 }
 
 void launch_residual_sumsq(const Level &L, double *partials, double *r_out, double r_scale,
-                           hipStream_t st) {
+                           hipStream_t st, const SumTail &tail) {
     if (L.n >= 128) { // periodic levels and the finest levels of refinements
-        residual_tiled<double>(L, partials, r_out, r_scale, st);
+        residual_tiled<double>(L, partials, r_out, r_scale, st, tail);
         return;
     }
+    const unsigned nb = reduce_blocks(L.cells(), tail);
+    const SumTail own = tail_in_launch(tail, nb);
     if (L.periodic)
-        k_residual_sumsq<true><<<kReduceBlocks, kBlock, 0, st>>>(
-            L.phi, L.s, make_ix<true>(L.n, L.lg), L.alpha, partials, r_out, r_scale, nullptr);
+        k_residual_sumsq<true><<<nb, kBlock, 0, st>>>(
+            L.phi, L.s, make_ix<true>(L.n, L.lg), L.alpha, partials, r_out, r_scale, nullptr, own);
     else
-        k_residual_sumsq<false><<<kReduceBlocks, kBlock, 0, st>>>(
-            L.phi, L.s, make_ix<false>(L.n, L.lg), L.alpha, partials, r_out, r_scale, L.mask);
+        k_residual_sumsq<false><<<nb, kBlock, 0, st>>>(
+            L.phi, L.s, make_ix<false>(L.n, L.lg), L.alpha, partials, r_out, r_scale, L.mask, own);
+    launch_sum_tail(tail, nb, partials, st);
 }
 
 bool residual_tiled_ok(const Level &L) { return L.periodic && L.n >= 128; }
 
-void launch_residual_tiled_to32(const Level &L, float *r32, double *partials, hipStream_t st) {
-    residual_tiled<float>(L, partials, r32, 1.0, st);
+void launch_residual_tiled_to32(const Level &L, float *r32, double *partials, hipStream_t st,
+                                const SumTail &tail) {
+    residual_tiled<float>(L, partials, r32, 1.0, st, tail);
 }
 
 void launch_partial_sums(const double *a, size_t count, bool squares, double *partials,
-                         hipStream_t st) {
-    k_partial_sums<<<kReduceBlocks, kBlock, 0, st>>>(a, count, squares ? 1 : 0, partials);
+                         hipStream_t st, const SumTail &tail) {
+    const unsigned nb = reduce_blocks(count, tail);
+    k_partial_sums<<<nb, kBlock, 0, st>>>(a, count, squares ? 1 : 0, partials,
+                                          tail_in_launch(tail, nb));
+    launch_sum_tail(tail, nb, partials, st);
+}
+
+void launch_publish(const unsigned *counters, unsigned *host, hipStream_t st) {
+    k_publish<<<1, 64, 0, st>>>(counters, host);
 }
 
 void launch_diff_partials(const double *a, const double *b, size_t count, double *partials,
@@ -1800,7 +1848,7 @@ void launch_diff_partials(const double *a, const double *b, size_t count, double
 }
 
 void launch_reduce_final(const double *partials, double *out, hipStream_t st) {
-    k_reduce_final<<<1, kBlock, 0, st>>>(partials, out);
+    k_reduce_final<<<1, kBlock, 0, st>>>(partials, kReduceBlocks, out, nullptr);
 }
 
 void launch_residual_norms(const double *sums, double *out, hipStream_t st) {
@@ -1926,6 +1974,15 @@ void launch_bottom_dir(const Level *H, int l, int nl, int nu1, int nu2, int cswe
 void launch_source(const double *delta, size_t count, const double *sum, double inv_count_mean,
                    double f, double *s, hipStream_t st) {
     k_source<<<blocks_for(count), kBlock, 0, st>>>(delta, count, sum, inv_count_mean, f, s);
+}
+
+void launch_source_sumsq(const double *delta, size_t count, const double *sum,
+                         double inv_count_mean, double f, double *s, double *partials,
+                         hipStream_t st, const SumTail &tail) {
+    const unsigned nb = reduce_blocks(count, tail);
+    k_source_sumsq<<<nb, kBlock, 0, st>>>(delta, count, sum, inv_count_mean, f, s, partials,
+                                          tail_in_launch(tail, nb));
+    launch_sum_tail(tail, nb, partials, st);
 }
 
 void launch_shift_by_mean(double *a, size_t count, const double *sum, hipStream_t st) {

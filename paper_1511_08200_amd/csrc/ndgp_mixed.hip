@@ -89,7 +89,7 @@ using IxP = Ix<true>;
 
 __global__ void __launch_bounds__(kBlock)
 k_residual_to32(const double *__restrict__ phi, const double *__restrict__ s, IxP ix, double al,
-                float *__restrict__ r32, double *__restrict__ partials) {
+                float *__restrict__ r32, double *__restrict__ partials, SumTail tail) {
     const int n = ix.n, lg = ix.lg;
     const int total = 1 << (3 * lg);
     double acc = 0.0;
@@ -101,8 +101,7 @@ k_residual_to32(const double *__restrict__ phi, const double *__restrict__ s, Ix
         acc = fma(r, r, acc);
         r32[c] = (float)r;
     }
-    const double b = block_sum(acc);
-    if (threadIdx.x == 0) partials[blockIdx.x] = b;
+    sum_tail(block_sum(acc), partials, tail);
 }
 
 __global__ void __launch_bounds__(kBlock)
@@ -743,13 +742,16 @@ inline IxP ixp(int n, int lg) { return IxP{n, lg, n + 2}; }
 
 } // namespace
 
-void launch_residual_to32(const Level &L, float *r32, double *partials, hipStream_t st) {
+void launch_residual_to32(const Level &L, float *r32, double *partials, hipStream_t st,
+                          const SumTail &tail) {
     if (residual_tiled_ok(L)) {
-        launch_residual_tiled_to32(L, r32, partials, st);
+        launch_residual_tiled_to32(L, r32, partials, st, tail);
         return;
     }
-    k_residual_to32<<<kReduceBlocks, kBlock, 0, st>>>(L.phi, L.s, ixp(L.n, L.lg), L.alpha, r32,
-                                                      partials);
+    const unsigned nb = nblocks(L.cells()); // at most 1024
+    k_residual_to32<<<nb, kBlock, 0, st>>>(L.phi, L.s, ixp(L.n, L.lg), L.alpha, r32, partials,
+                                          tail_in_launch(tail, nb));
+    launch_sum_tail(tail, nb, partials, st);
 }
 
 void launch_to32(const double *a, float *b, size_t count, hipStream_t st) {

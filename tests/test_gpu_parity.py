@@ -673,6 +673,23 @@ def test_total_force_and_geff_stats_match_oracle():
         ndgp.geff_stats(grid, [dev(x) for x in phis], [dev(x) for x in psis], edges[::-1])
 
 
+@pytest.mark.parametrize("n", [8, 16, 32, 64, 128])
+def test_reported_norm_equals_residual_entry_point(n):
+    """The norm a solve stops on (added up by the launch's last block up to 256
+    blocks, by a launch of its own beyond) is the residual entry point's.  At
+    a residual of 1e-4 the gauge shift's rounding (1e-15 of the source) moves it
+    by about 1e-11 of its value."""
+    f = synth.make_field(n, 1.0, 23)
+    grid = ndgp.Grid(n=n, h=ndgp.cell_size(float(n), n))
+    params = ndgp.Params(rc=1.0, tol=1e-4)
+    for seed in range(3):  # one solve after the other on the same workspace
+        d = dev(np.roll(f.delta, seed, axis=0))
+        phi, rep = ndgp.solve(grid, params, [d])
+        _, rel_norm = ndgp.residual(grid, params, [d], phi[0], want_r=False)
+        assert rep.rel_res[0] == pytest.approx(rel_norm, rel=1e-9)
+        assert rep.rel_res[0] == rep.history[-1] if rep.history else True
+
+
 def test_patch_residual_level():
     """ndgp_residual on a patch level uses the ghost shell as boundary."""
     f, deltas, grid = patch_problem()
