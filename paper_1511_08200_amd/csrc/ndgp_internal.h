@@ -308,6 +308,7 @@ struct TileArgs {
     T al_c;
 };
 void launch_tile(const TileArgs<double> &a, int sweeps, bool pro, bool rest, hipStream_t st);
+void launch_tile(const TileArgs<float> &a, int sweeps, bool pro, bool rest, hipStream_t st);
 // s = f * (delta - sum[0] * inv_count_mean)     (sum: device scalar)
 void launch_source(const double *delta, size_t count, const double *sum, double inv_count_mean,
                    double f, double *s, hipStream_t st);

@@ -503,7 +503,7 @@ struct Runner {
         for (int l = 1; l < nl; ++l) launch_avg32(H32[l - 1], H32[l], st);
         // the correction starts from zero: the first fused sweep takes it as
         // such without reading it, else it is filled
-        const bool from_zero = corr_first_sweep_from_zero(H32[0]);
+        const bool from_zero = nl > 1 && corr_first_sweep_from_zero(H32[0]);
         if (!from_zero) launch_fill32(H32[0].e, cells, 0.f, st);
         for (int q = 0; q < kMixedInner; ++q) corr_vcycle(H32, nl, 0, from_zero && q == 0);
         launch_add_to32(H[0].phi, H32[0].e, H32[0].phi, cells, st);
@@ -642,10 +642,43 @@ struct Runner {
     // ---- mixed precision: FP32 FAS on the correction e of
     //      L[phi + e] - L[phi] = r, inside an FP64 defect-correction loop
     // as smooth(): fused sweeps on large levels, an odd last sweep in two
-    // launches.  (Adding the coarse-grid correction on load, as the FP64
-    // sweep does, spills registers here and is slower than its own launch.)
+    // launches
     bool corr_first_sweep_from_zero(const Level32 &L) const {
-        return !(P.c.flags & NDGP_TWO_PASS) && corr_fused_ok(L) && P.c.nu1 >= 2;
+        return !(P.c.flags & NDGP_TWO_PASS) &&
+               (corr_tile_ok(L) || (corr_fused_ok(L) && P.c.nu1 >= 2));
+    }
+
+    // as tile_ok and tile_sweeps, for the correction; from_zero: it is zero before
+    // the first sweep, which does not read it
+    bool corr_tile_ok(const Level32 &L) const {
+        return !(P.c.flags & NDGP_TWO_PASS) && L.n >= 16 && L.n <= 64;
+    }
+
+    void corr_tile_sweeps(Level32 &L, Level32 &C, int sweeps, int launches, bool up,
+                          bool from_zero) {
+        for (int q = 0, done = 0; q < launches; ++q) {
+            const int k = sweeps - done - (launches - 1 - q) >= 2 ? 2 : 1;
+            TileArgs<float> a{};
+            a.pin = L.e;
+            a.pout = L.ealt;
+            a.base = L.phi;
+            a.s = L.r;
+            a.lg = L.lg;
+            a.al = (float)L.alpha;
+            a.w = L.omega;
+            a.events = P.fallbacks;
+            a.from_zero = from_zero && q == 0;
+            a.phi_c = C.e;
+            a.hat_c = C.ehat;
+            a.hat_out = C.ehat;
+            a.s_out = C.r;
+            a.phi_out = C.e;
+            a.base_c = C.phi;
+            a.al_c = (float)C.alpha;
+            launch_tile(a, k, up && q == 0, !up && q == launches - 1, st);
+            std::swap(L.e, L.ealt);
+            done += k;
+        }
     }
 
     // with C the coarse-grid correction from C is added first: on load in
@@ -684,8 +717,16 @@ struct Runner {
             launch_corr_coarsest(L, coarsest_sweeps(L.omega == kDampedStep), P.fallbacks, st);
             return;
         }
-        corr_smooth(L, P.c.nu1, nullptr, from_zero);
         Level32 &C = H[l + 1];
+        if (corr_tile_ok(L)) {
+            int down, up;
+            tile_split(P.c.nu1, P.c.nu2, down, up);
+            corr_tile_sweeps(L, C, P.c.nu1, down, false, from_zero);
+            corr_vcycle(H, nl, l + 1);
+            corr_tile_sweeps(L, C, P.c.nu2, up, true, false);
+            return;
+        }
+        corr_smooth(L, P.c.nu1, nullptr, from_zero);
         launch_corr_restrict(L, C, !(P.c.flags & NDGP_TWO_PASS), st);
         launch_corr_coarse_source(C, st);
         corr_vcycle(H, nl, l + 1);

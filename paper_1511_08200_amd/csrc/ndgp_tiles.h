@@ -2,7 +2,7 @@
 // field they relax.  Not part of the public ABI.
 #pragma once
 
-#include "ndgp_device.h"
+#include "ndgp_corr.h"
 
 namespace ndgp {
 
@@ -25,6 +25,23 @@ struct TileField {
     }
     __device__ __forceinline__ static double apply(const double v[19], const double *, double al) {
         return dev::apply_L(dev::stencil_terms(v), al);
+    }
+};
+
+// the FP32 correction of the mixed-precision solve, about a static FP32 field
+struct TileCorrection {
+    using T = float;
+    using Pair = float2;
+    static constexpr bool two = true;
+    __device__ __forceinline__ static float fma_(float a, float b, float c) {
+        return fmaf(a, b, c);
+    }
+    __device__ __forceinline__ static float relax(const float v[19], const float vb[19], float r,
+                                                  float al, double w, unsigned &ev) {
+        return dev::relax_corr_cell(vb, v, r, al, w, ev);
+    }
+    __device__ __forceinline__ static float apply(const float v[19], const float vb[19], float al) {
+        return dev::corr_terms(vb, v, al).A;
     }
 };
 

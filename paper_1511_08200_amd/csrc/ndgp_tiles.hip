@@ -284,4 +284,8 @@ void launch_tile(const TileArgs<double> &a, int sweeps, bool pro, bool rest, hip
     tile_level<TileField>(a, sweeps, pro, rest, st);
 }
 
+void launch_tile(const TileArgs<float> &a, int sweeps, bool pro, bool rest, hipStream_t st) {
+    tile_level<TileCorrection>(a, sweeps, pro, rest, st);
+}
+
 } // namespace ndgp
