@@ -415,6 +415,15 @@ ndgp_status ndgp_cic_density(const ndgp_grid *grid, const double *pos, int64_t n
 ndgp_status ndgp_cic_force(const ndgp_grid *grid, const double *const force[1 + NDGP_MAX_PATCHES],
                            const double *pos, int64_t n_particles, double *out,
                            hipStream_t stream);
+/* ndgp_cic_force with scratch for the domain's force components side by side,
+   which particles in no spatial order read about twice as fast (same bits).
+   ndgp_cic_force_workspace_bytes: the bytes it can use, 0 where it would use none
+   (few particles; also for invalid arguments).  A smaller or NULL workspace is
+   not used. */
+size_t ndgp_cic_force_workspace_bytes(const ndgp_grid *grid, int64_t n_particles);
+ndgp_status ndgp_cic_force_in(const ndgp_grid *grid, const double *const force[1 + NDGP_MAX_PATCHES],
+                              const double *pos, int64_t n_particles, double *out, void *workspace,
+                              size_t workspace_bytes, hipStream_t stream);
 
 /*
  * Serving: the same solve as ndgp_solve, split into non-blocking steps so that

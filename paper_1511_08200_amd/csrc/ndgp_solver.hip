@@ -1693,8 +1693,17 @@ ndgp_status refine_flags_impl(const ndgp_grid *grid, const double *const delta[]
     return NDGP_OK;
 }
 
+size_t carve_cic_force(const Cfg &c, char *base, double **lines, unsigned **off) {
+    Carver cv{base};
+    double *l = cv.take<double>(3 * (size_t)c.n * c.n * c.n);
+    unsigned *o = cv.take<unsigned>(1);
+    if (lines) *lines = l;
+    if (off) *off = o;
+    return cv.off + 256;
+}
+
 ndgp_status cic_force_impl(const ndgp_grid *grid, const double *const force[], const double *pos,
-                           int64_t np, double *out, hipStream_t st) {
+                           int64_t np, double *out, void *ws, size_t ws_bytes, hipStream_t st) {
     Cfg c;
     std::string why;
     if (!resolve_grid(grid, c, why)) return fail(NDGP_EINVAL, why);
@@ -1714,7 +1723,13 @@ ndgp_status cic_force_impl(const ndgp_grid *grid, const double *const force[], c
         for (int a = 0; a < 3; ++a) lv.corner[l][a] = corner[l][a];
         lv.force[l] = force[l];
     }
-    launch_cic_gather(pos, (long long)np, lv, out, st);
+    // a workspace is optional, and so is its use
+    double *lines = nullptr;
+    unsigned *off = nullptr;
+    if (ws && ws_bytes >= carve_cic_force(c, nullptr, nullptr, nullptr) &&
+        cic_gather_lines((long long)np, c.n))
+        carve_cic_force(c, aligned_base(ws), &lines, &off);
+    launch_cic_gather(pos, (long long)np, lv, lines, off, out, st);
     HIP_TRY(hipGetLastError());
     return NDGP_OK;
 }
@@ -2047,7 +2062,28 @@ ndgp_status ndgp_cic_density(const ndgp_grid *grid, const double *pos, int64_t n
 ndgp_status ndgp_cic_force(const ndgp_grid *grid, const double *const force[1 + NDGP_MAX_PATCHES],
                            const double *pos, int64_t n_particles, double *out,
                            hipStream_t stream) {
-    return guarded([&] { return cic_force_impl(grid, force, pos, n_particles, out, stream); });
+    return guarded(
+        [&] { return cic_force_impl(grid, force, pos, n_particles, out, nullptr, 0, stream); });
+}
+
+size_t ndgp_cic_force_workspace_bytes(const ndgp_grid *grid, int64_t n_particles) {
+    Cfg c;
+    std::string why;
+    if (!resolve_grid(grid, c, why)) {
+        g_err = why;
+        return 0;
+    }
+    return cic_gather_lines((long long)n_particles, c.n)
+               ? carve_cic_force(c, nullptr, nullptr, nullptr)
+               : 0;
+}
+
+ndgp_status ndgp_cic_force_in(const ndgp_grid *grid, const double *const force[1 + NDGP_MAX_PATCHES],
+                              const double *pos, int64_t n_particles, double *out, void *workspace,
+                              size_t workspace_bytes, hipStream_t stream) {
+    return guarded([&] {
+        return cic_force_impl(grid, force, pos, n_particles, out, workspace, workspace_bytes, stream);
+    });
 }
 
 ndgp_status ndgp_refine_flags(const ndgp_grid *grid, const double *const delta[1 + NDGP_MAX_PATCHES],

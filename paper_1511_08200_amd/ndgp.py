@@ -123,6 +123,11 @@ def lib():
                                        ctypes.c_size_t, vp]
         L.ndgp_cic_force.restype = ctypes.c_int
         L.ndgp_cic_force.argtypes = [ctypes.POINTER(_Grid), arr3, vp, ctypes.c_int64, vp, vp]
+        L.ndgp_cic_force_workspace_bytes.restype = ctypes.c_size_t
+        L.ndgp_cic_force_workspace_bytes.argtypes = [ctypes.POINTER(_Grid), ctypes.c_int64]
+        L.ndgp_cic_force_in.restype = ctypes.c_int
+        L.ndgp_cic_force_in.argtypes = [ctypes.POINTER(_Grid), arr3, vp, ctypes.c_int64, vp, vp,
+                                        ctypes.c_size_t, vp]
         L.ndgp_refine_flags.restype = ctypes.c_int
         L.ndgp_refine_flags.argtypes = [ctypes.POINTER(_Grid), arr3, ctypes.c_int64,
                                         ctypes.c_double, arr3, ctypes.POINTER(ctypes.c_int64),
@@ -686,8 +691,13 @@ def cic_force(grid: Grid, force: Sequence[torch.Tensor], pos: torch.Tensor, out=
         out = torch.empty((3, npart), dtype=torch.float64, device=pos.device)
     fptr = [_dev(force[l], (3,) + (grid.level_n(l),) * 3, f"force[{l}]")
             for l in range(1 + len(grid.patches))]
-    _check(lib().ndgp_cic_force(ctypes.byref(g), _arr3(fptr), _dev(pos, (3, npart), "pos"),
-                                npart, _dev(out, (3, npart), "out"), _stream(stream)))
+    # many particles: scratch that lets them read the components side by side
+    nb = int(lib().ndgp_cic_force_workspace_bytes(ctypes.byref(g), npart))
+    ws = workspace(nb, pos.device, stream) if nb else None
+    _check(lib().ndgp_cic_force_in(ctypes.byref(g), _arr3(fptr), _dev(pos, (3, npart), "pos"),
+                                   npart, _dev(out, (3, npart), "out"),
+                                   ws.data_ptr() if ws is not None else None,
+                                   ws.numel() if ws is not None else 0, _stream(stream)))
     return out
 
 

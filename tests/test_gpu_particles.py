@@ -122,6 +122,33 @@ def test_binned_deposit_equals_direct_atomics(n, m, count, where):
     assert abs(float(got[0].mean())) <= 1e-10
 
 
+@pytest.mark.parametrize("n,m,count,ordered", [
+    (64, 32, 262144, False),   # the fewest particles that interleave the components
+    (64, 32, 262145, True),    # particles in cell order: the sample decides against it
+    (64, 0, 262143, False),    # too few
+    (128, 64, 300007, False),
+])
+def test_interleaved_gather_equals_component_gather(n, m, count, ordered):
+    """The gather with a workspace (components side by side) gives the bits of
+    the one without, on the domain and where a patch holds the particle."""
+    say(f"gather n={n} patch={m} particles={count} ordered={ordered}")
+    f = synth.make_field(64, 1.5, 4)
+    pos = dev(synth.make_particles(f, count, 9, cell_order=ordered))
+    patches = [ndgp.Patch(m, (n - m // 4, -3, n // 2))] if m else []  # wraps the domain
+    grid = ndgp.Grid(n=n, h=ndgp.cell_size(float(n), n), patches=patches)
+    rng = np.random.default_rng(5)
+    forces = [dev(rng.standard_normal((3,) + (grid.level_n(l),) * 3))
+              for l in range(1 + len(patches))]
+    got = ndgp.cic_force(grid, forces, pos)
+    want = torch.full_like(got, float("nan"))
+    g = grid._c()
+    status = ndgp.lib().ndgp_cic_force(g, ndgp._arr3([x.data_ptr() for x in forces]),
+                                       pos.data_ptr(), count, want.data_ptr(), ndgp._stream(None))
+    torch.cuda.synchronize()
+    assert status == ndgp.NDGP_OK
+    assert torch.equal(got, want)
+
+
 def test_cic_rejects_bad_arguments():
     grid = ndgp.Grid(n=32, h=ndgp.cell_size(32.0, 32))
     with pytest.raises(ValueError):
