@@ -271,22 +271,6 @@ struct BottomLevels {
 bool bottom_ok(const Level *H, int l, int nl);
 void launch_bottom(const Level *H, int l, int nl, int nu1, int nu2, int csweeps,
                    unsigned *fallbacks, hipStream_t st);
-// The same for the coarse levels of a refinement (padded, ghost shells that
-// follow the interior, held cells): level l (n <= 16) and every coarser level.
-struct BottomDirLevels {
-    int levels;                                 // l .. nl-1
-    int lg0;                                    // log2(n) of level l
-    double alpha[kBottomMaxLevels];
-    double omega, omega_c;
-    double *phi0;                               // level l: in/out, padded
-    const double *s0;                           // level l: natural
-    const double *hat[kBottomMaxLevels];        // padded (ghost shells; interiors of
-                                                // the coarser levels are recomputed)
-    const unsigned char *mask[kBottomMaxLevels]; // natural, or null (none held)
-};
-bool bottom_dir_ok(const Level *H, int l, int nl);
-void launch_bottom_dir(const Level *H, int l, int nl, int nu1, int nu2, int csweeps,
-                       unsigned *fallbacks, hipStream_t st);
 // `sweeps` (1 or 2) red-black sweeps of a periodic level of 16^3 to 64^3 cells in
 // one launch (ndgp_tiles.hip), pin -> pout; pro: starting from pin + P(phi_c -
 // hat_c); rest: followed by the FAS restriction and coarse source into hat_out,
@@ -309,6 +293,21 @@ struct TileArgs {
 };
 void launch_tile(const TileArgs<double> &a, int sweeps, bool pro, bool rest, hipStream_t st);
 void launch_tile(const TileArgs<float> &a, int sweeps, bool pro, bool rest, hipStream_t st);
+// the same for a refinement's levels (padded; coarse levels' ghosts follow the
+// interior: dyn and hat; held cells: mask, natural or null)
+struct TileDirArgs {
+    const double *pin;
+    double *pout;
+    const double *s, *hat;
+    const unsigned char *mask;
+    int lg, dyn;
+    double al, w;
+    unsigned *events;
+    const double *phi_c, *hat_c;
+    double *hat_out, *s_out, *phi_out;
+    double al_c;
+};
+void launch_tile_dir(const TileDirArgs &a, int sweeps, bool pro, bool rest, hipStream_t st);
 // s = f * (delta - sum[0] * inv_count_mean)     (sum: device scalar)
 void launch_source(const double *delta, size_t count, const double *sum, double inv_count_mean,
                    double f, double *s, hipStream_t st);

@@ -1225,186 +1225,6 @@ k_bottom(double *__restrict__ phi, const double *__restrict__ s, int lg0, Bottom
     if (fb) flush_events(fallbacks, fb);
 }
 
-// The bottom of a refinement's V-cycle in one workgroup: its coarse levels
-// from one of at most 16^3 cells down to the coarsest, padded with their
-// ghost shells, all arrays in LDS.  Each step has the arithmetic, in the same
-// order, of the per-level kernels of those levels (k_smooth_half,
-// k_restrict_residual, k_coarse_source, k_coarsest, k_prolong8), so the result
-// is bit for bit theirs.  Those kernels rewrite the ghosts of every cell they
-// write from its new value (write_owned_ghosts); a ghost is thus always the
-// same function of its interior cell's current value, and the half sweeps
-// here, done in place (new values of one colour into registers, wait, store),
-// rewrite only the ghosts of the cells they change.  Held cells (mask 0) keep
-// their values, take no residual and no correction.
-constexpr int kBottomDirThreads = 1024;
-constexpr int kBottomDirPerThread = 2048 / kBottomDirThreads; // cells of one colour at 16^3
-constexpr int kBottomDirPad = 18 * 18 * 18 + 10 * 10 * 10 + 6 * 6 * 6 + 4 * 4 * 4;
-constexpr int kBottomDirCells = 4096 + 512 + 64 + 8;
-
-__global__ void __launch_bounds__(kBottomDirThreads)
-k_bottom_dir(BottomDirLevels bl, int nu1, int nu2, int csweeps, unsigned *__restrict__ fallbacks) {
-    __shared__ double PHI[kBottomDirPad];
-    __shared__ double HAT[kBottomDirPad];
-    __shared__ double SRC[kBottomDirCells];
-    __shared__ unsigned char MSK[kBottomDirCells];
-    const int tid = threadIdx.x;
-    const int nb = bl.levels, lg0 = bl.lg0;
-    auto pad = [&](int q) {
-        const int m = (1 << (lg0 - q)) + 2;
-        return m * m * m;
-    };
-    // level q starts at poff(q) in PHI and HAT, at coff(q) in SRC and MSK
-    auto poff = [&](int q) {
-        int o = 0;
-        for (int p = 0; p < q; ++p) o += pad(p);
-        return o;
-    };
-    auto coff = [&](int q) {
-        int o = 0;
-        for (int p = 0; p < q; ++p) o += 1 << (3 * (lg0 - p));
-        return o;
-    };
-    auto alpha = [&](int q) {
-        return q == 0 ? bl.alpha[0] : q == 1 ? bl.alpha[1] : q == 2 ? bl.alpha[2] : bl.alpha[3];
-    };
-    auto ixq = [&](int q) {
-        const int lg = lg0 - q;
-        return Ix<false>{1 << lg, lg, (1 << lg) + 2};
-    };
-    unsigned fb = 0;
-    for (int q = 0; q < nb; ++q) {
-        const double *hg = q == 0 ? bl.hat[0] : q == 1 ? bl.hat[1] : q == 2 ? bl.hat[2] : bl.hat[3];
-        const unsigned char *mg =
-            q == 0 ? bl.mask[0] : q == 1 ? bl.mask[1] : q == 2 ? bl.mask[2] : bl.mask[3];
-        double *hl = HAT + poff(q);
-        for (int t = tid; t < pad(q); t += kBottomDirThreads) hl[t] = hg[t];
-        unsigned char *ml = MSK + coff(q);
-        for (int t = tid; t < (1 << (3 * (lg0 - q))); t += kBottomDirThreads)
-            ml[t] = mg ? mg[t] : (unsigned char)1;
-    }
-    for (int t = tid; t < pad(0); t += kBottomDirThreads) PHI[t] = bl.phi0[t];
-    for (int t = tid; t < (1 << (3 * lg0)); t += kBottomDirThreads) SRC[t] = bl.s0[t];
-    __syncthreads();
-
-    auto smooth = [&](int q, int sweeps) {
-        const Ix<false> ix = ixq(q);
-        const int lg = ix.lg, n = ix.n, half = n >> 1;
-        double *ph = PHI + poff(q);
-        const double *hh = HAT + poff(q);
-        const double *sr = SRC + coff(q);
-        const unsigned char *mk = MSK + coff(q);
-        const double al = alpha(q), w = q == nb - 1 ? bl.omega_c : bl.omega;
-        const int ncol = (n * n * n) >> 1; // cells of one colour
-        for (int sw = 0; sw < sweeps; ++sw)
-            for (int col = 0; col < 2; ++col) {
-                double v[kBottomDirPerThread];
-                int cell[kBottomDirPerThread]; // natural index, or -1: nothing to store
-#pragma unroll
-                for (int c = 0; c < kBottomDirPerThread; ++c) {
-                    v[c] = 0.0;
-                    cell[c] = -1;
-                    const int t = tid + c * kBottomDirThreads;
-                    if (t < ncol) {
-                        const int m = t & (half - 1);
-                        const int row = t >> (lg - 1);
-                        const int j = row & (n - 1), k = row >> lg;
-                        const int i = 2 * m + ((col ^ j ^ k) & 1);
-                        const int nat = ((k << lg) + j) * n + i;
-                        if (mk[nat]) { // a held cell keeps its value (and its ghosts)
-                            double g[19];
-                            gather(ph, ix, i, j, k, g);
-                            v[c] = relax_cell(g, sr[nat], al, w, fb);
-                            cell[c] = nat;
-                        }
-                    }
-                    __builtin_amdgcn_sched_barrier(0); // one cell at a time: no spills
-                }
-                __syncthreads();
-#pragma unroll
-                for (int c = 0; c < kBottomDirPerThread; ++c)
-                    if (cell[c] >= 0) {
-                        const int i = cell[c] & (n - 1), j = (cell[c] >> lg) & (n - 1),
-                                  k = cell[c] >> (2 * lg);
-                        ph[ix(i, j, k)] = v[c];
-                        write_owned_ghosts(ph, hh, ix, i, j, k, v[c]);
-                    }
-                __syncthreads();
-            }
-    };
-
-    for (int q = 0; q + 1 < nb; ++q) {
-        smooth(q, nu1);
-        const Ix<false> ixf = ixq(q), ixc = ixq(q + 1);
-        const int nc = ixc.n, lgc = ixc.lg;
-        double *pc = PHI + poff(q + 1), *hc = HAT + poff(q + 1), *sc = SRC + coff(q + 1);
-        for (int t = tid; t < nc * nc * nc; t += kBottomDirThreads) {
-            const int I = t & (nc - 1), J = (t >> lgc) & (nc - 1), K = t >> (2 * lgc);
-            // restrict_cell's sums (children in its order), each child's
-            // stencil gathered on its own
-            const double *pf = PHI + poff(q), *sf = SRC + coff(q);
-            const unsigned char *mf = MSK + coff(q);
-            const int nf = ixf.n;
-            double sphi = 0.0, sr = 0.0;
-#pragma unroll 1
-            for (int ch = 0; ch < 8; ++ch) {
-                const int fi = 2 * I + (ch & 1), fj = 2 * J + ((ch >> 1) & 1), fk = 2 * K + (ch >> 2);
-                double v[19];
-                gather(pf, ixf, fi, fj, fk, v);
-                const int fc = (fk * nf + fj) * nf + fi;
-                const double r = !mf[fc] ? 0.0 : sf[fc] - apply_L(stencil_terms(v), alpha(q));
-                sphi += v[0];
-                sr += r;
-            }
-            hc[ixc(I, J, K)] = sphi * 0.125;
-            sc[t] = sr * 0.5;
-        }
-        __syncthreads();
-        for (int t = tid; t < nc * nc * nc; t += kBottomDirThreads) {
-            const int i = t & (nc - 1), j = (t >> lgc) & (nc - 1), k = t >> (2 * lgc);
-            double v[19];
-            gather(hc, ixc, i, j, k, v);
-            sc[t] = apply_L(stencil_terms(v), alpha(q + 1)) + sc[t];
-            pc[ixc(i, j, k)] = v[0];
-            write_owned_ghosts(pc, hc, ixc, i, j, k, v[0]); // zero correction
-        }
-        __syncthreads();
-    }
-    smooth(nb - 1, csweeps);
-    for (int q = nb - 2; q >= 0; --q) {
-        const Ix<false> ixf = ixq(q), ixc = ixq(q + 1);
-        const int nf = ixf.n, lgf = ixf.lg;
-        const double *pc = PHI + poff(q + 1), *hc = HAT + poff(q + 1);
-        double *pf = PHI + poff(q);
-        const double *hf = HAT + poff(q);
-        const unsigned char *mk = MSK + coff(q);
-        for (int t = tid; t < nf * nf * nf; t += kBottomDirThreads) {
-            if (!mk[t]) continue; // held: no correction
-            const int i = t & (nf - 1), j = (t >> lgf) & (nf - 1), k = t >> (2 * lgf);
-            const int I = i >> 1, J = j >> 1, K = k >> 1;
-            const int si = (i & 1) ? 1 : -1, sj = (j & 1) ? 1 : -1, sk = (k & 1) ? 1 : -1;
-            double acc = 0.0;
-#pragma unroll
-            for (int c = 0; c < 2; ++c)
-#pragma unroll
-                for (int b = 0; b < 2; ++b)
-#pragma unroll
-                    for (int a = 0; a < 2; ++a) {
-                        const double w = (a ? 0.25 : 0.75) * (b ? 0.25 : 0.75) * (c ? 0.25 : 0.75);
-                        const int qq = ixc(I + a * si, J + b * sj, K + c * sk);
-                        acc = fma(w, pc[qq] - hc[qq], acc);
-                    }
-            const int me = ixf(i, j, k);
-            const double val = pf[me] + acc;
-            pf[me] = val;
-            write_owned_ghosts(pf, hf, ixf, i, j, k, val);
-        }
-        __syncthreads();
-        smooth(q, nu2);
-    }
-    for (int t = tid; t < pad(0); t += kBottomDirThreads) bl.phi0[t] = PHI[t];
-    if (fb) flush_events(fallbacks, fb);
-}
-
 __global__ void __launch_bounds__(kBlock)
 k_source(const double *__restrict__ delta, size_t count, const double *__restrict__ sum,
          double inv_count_mean, double f, double *__restrict__ s) {
@@ -1945,30 +1765,6 @@ void launch_bottom(const Level *H, int l, int nl, int nu1, int nu2, int csweeps,
     bl.omega_c = H[nl - 1].omega;
     k_bottom<<<1, kBottomThreads, 0, st>>>(H[l].phi, H[l].s, H[l].lg, bl, nu1, nu2, csweeps,
                                            fallbacks);
-}
-
-bool bottom_dir_ok(const Level *H, int l, int nl) {
-    if (l + 1 >= nl || nl - l > kBottomMaxLevels) return false;
-    for (int q = l; q < nl; ++q)
-        if (H[q].periodic || !H[q].dyn_bc) return false;
-    return H[l].n <= 16 && H[nl - 1].n >= 2;
-}
-
-void launch_bottom_dir(const Level *H, int l, int nl, int nu1, int nu2, int csweeps,
-                       unsigned *fallbacks, hipStream_t st) {
-    BottomDirLevels bl{};
-    bl.levels = nl - l;
-    bl.lg0 = H[l].lg;
-    bl.omega = H[l].omega;
-    bl.omega_c = H[nl - 1].omega;
-    bl.phi0 = H[l].phi;
-    bl.s0 = H[l].s;
-    for (int q = 0; q < bl.levels; ++q) {
-        bl.alpha[q] = H[l + q].alpha;
-        bl.hat[q] = H[l + q].hat;
-        bl.mask[q] = H[l + q].mask;
-    }
-    k_bottom_dir<<<1, kBottomDirThreads, 0, st>>>(bl, nu1, nu2, csweeps, fallbacks);
 }
 
 void launch_source(const double *delta, size_t count, const double *sum, double inv_count_mean,

@@ -559,7 +559,7 @@ struct Runner {
     // sweeps are faster (they relax 1.16 times the cells, not 2.9).  A timed level
     // keeps the launches that are timed.
     bool tile_ok(const Level &L) const {
-        return !(P.c.flags & NDGP_TWO_PASS) && L.periodic && L.n >= 16 && L.n <= 64 &&
+        return !(P.c.flags & NDGP_TWO_PASS) && L.n >= 16 && L.n <= 64 &&
                !(timer && timer->on && L.s == timed_s);
     }
 
@@ -570,6 +570,15 @@ struct Runner {
         for (int q = 0, done = 0; q < launches; ++q) {
             const int k = sweeps - done - (launches - 1 - q) >= 2 ? 2 : 1;
             const bool pro = up && q == 0, rest = !up && q == launches - 1;
+            if (!L.periodic) {
+                const TileDirArgs a{L.phi, L.alt, L.s, L.hat, L.mask, L.lg, L.dyn_bc ? 1 : 0,
+                                    L.alpha, L.omega, P.fallbacks, C.phi, C.hat, C.hat, C.s, C.phi,
+                                    C.alpha};
+                launch_tile_dir(a, k, pro, rest, st);
+                std::swap(L.phi, L.alt);
+                done += k;
+                continue;
+            }
             TileArgs<double> a{};
             a.pin = L.phi;
             a.pout = L.alt;
@@ -599,11 +608,6 @@ struct Runner {
         if (!tile_ok(L) && !(P.c.flags & NDGP_TWO_PASS) && bottom_ok(H, l, nl)) {
             launch_bottom(H, l, nl, P.c.nu1, P.c.nu2, coarsest_sweeps(L.omega == kDampedStep),
                           P.fallbacks, st);
-            return;
-        }
-        if (!(P.c.flags & NDGP_TWO_PASS) && bottom_dir_ok(H, l, nl)) {
-            launch_bottom_dir(H, l, nl, P.c.nu1, P.c.nu2, coarsest_sweeps(L.omega == kDampedStep),
-                              P.fallbacks, st);
             return;
         }
         Level &C = H[l + 1];
@@ -820,10 +824,10 @@ PatchOutcome relax_patch(Runner &run, Level *H, int nlev, const double *parent, 
     // with held cells the partner array holds their values too (blocks of held
     // cells are never written again)
     launch_interpolate(parent, npar, parent_periodic, b0, H[0].alt, H[0].active == nullptr, st);
+    // the coarse levels' hat shells; their fields' shells follow the interior and
+    // are written with it
     for (int l = 1; l < nlev; ++l) {
         ChildBox bm{{origin[0], origin[1], origin[2]}, l, m >> l};
-        launch_interpolate(parent, npar, parent_periodic, bm, H[l].phi, true, st);
-        launch_interpolate(parent, npar, parent_periodic, bm, H[l].alt, true, st);
         launch_interpolate(parent, npar, parent_periodic, bm, H[l].hat, true, st);
     }
     const size_t cq = (size_t)m * m * m;

@@ -673,6 +673,46 @@ def test_total_force_and_geff_stats_match_oracle():
         ndgp.geff_stats(grid, [dev(x) for x in phis], [dev(x) for x in psis], edges[::-1])
 
 
+@pytest.mark.parametrize("m,depth,nu1,nu2,threshold", [
+    (16, 2, 2, 2, None), (32, 2, 1, 2, None), (64, 1, 3, 3, None), (128, 1, 2, 1, None),
+    (32, 2, 2, 3, 0.1), (64, 1, 2, 2, 0.1),
+])
+def test_patch_tile_levels_bitwise_equal_per_level_launches(m, depth, nu1, nu2, threshold):
+    """A refinement's levels of 16^3 to 64^3 cells swept tile by tile, with fixed
+    and with following ghosts, held cells, and every split of the sweeps into
+    launches: the same bits and events as one launch per colour and transfer."""
+    say(f"patch tile levels m={m} depth={depth} nu={nu1},{nu2} threshold={threshold}")
+    n, rc = 32 if m <= 32 else 64, 2.0
+    f = synth.make_field(n, 2.0, 41, n_tophats=n // 8)
+    c, chain, patches, dd = synth.densest_tophat_centre(f), [], [], [dev(f.delta)]
+    for q in range(depth):
+        o = synth.patch_origin_centred(c, m // 2)
+        if q:
+            o = tuple(min(max(v, m // 4), m // 4) for v in o)
+        chain.append(o)
+        patches.append(ndgp.Patch(m, o))
+        dd.append(dev(synth.patch_delta(f, n, chain, m)))
+        c = tuple((c[a] - o[a]) * 2 for a in range(3))
+    grid = ndgp.Grid(n=n, h=ndgp.cell_size(float(n), n), patches=patches)
+    psi = None
+    if threshold is not None:
+        beta = ndgp.beta_lcdm(1.0, 0.3, rc)
+        psi = [1.5 * beta * p for p in ndgp.solve(grid, ndgp.Params(rc=0.0, beta=beta), dd)[0]]
+    out = []
+    for two_pass in (False, True):
+        p = ndgp.Params(rc=rc, tol=1e-10, nu1=nu1, nu2=nu2, two_pass=two_pass)
+        out.append(ndgp.solve(grid, p, dd, check=False) if psi is None else
+                   ndgp.solve_cellwise(grid, p, dd, psi, threshold, check=False))
+    (a, ra), (b, rb) = out
+    torch.cuda.synchronize()
+    say(f"  cycles={ra.cycles} iterated={ra.iterated_fraction[:3]} status={ra.status}")
+    assert ra.status == 0 and rb.status == 0
+    assert ra.cycles == rb.cycles and ra.rel_res == rb.rel_res
+    assert ra.holds == rb.holds and ra.fallbacks == rb.fallbacks
+    for x, y in zip(a, b):
+        assert torch.equal(x, y)
+
+
 @pytest.mark.parametrize("n", [8, 16, 32, 64, 128])
 def test_reported_norm_equals_residual_entry_point(n):
     """The norm a solve stops on (added up by the launch's last block up to 256
