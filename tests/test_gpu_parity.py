@@ -673,6 +673,34 @@ def test_total_force_and_geff_stats_match_oracle():
         ndgp.geff_stats(grid, [dev(x) for x in phis], [dev(x) for x in psis], edges[::-1])
 
 
+@pytest.mark.parametrize("n,m", [(128, 128), (64, 128), (128, 16)])
+def test_geff_stats_of_levels_a_thread_visits_twice(n, m):
+    """128^3 cells are two per thread of the G_eff reduction's fixed grid (fewer cells
+    leave a thread's second one out): counts, histogram, min and max exact, sums to
+    the rounding of 2e6 addends, with and without cells covered by a patch."""
+    from oracle import geff as G
+    grid = ndgp.Grid(n=n, h=1.0, patches=[ndgp.Patch(m, (7, 0, 21))] if m <= n else [])
+    if m > n:  # the domain alone
+        m = 0
+    rng = np.random.default_rng(n + m)
+    phis = [rng.standard_normal((n,) * 3)] + ([rng.standard_normal((m + 2,) * 3)] if m else [])
+    psis = [rng.standard_normal((n,) * 3)] + ([rng.standard_normal((m + 2,) * 3)] if m else [])
+    phis[0][3, 4, 5:9] = psis[0][3, 4, 5:9] = 0.25
+    edges = np.geomspace(1e-2, 10.0, 23)
+    got, hist = ndgp.geff_stats(grid, [dev(x) for x in phis], [dev(x) for x in psis], edges)
+    want, hist_o = G.geff_stats(phis, psis, [p.origin for p in grid.patches],
+                                [p.n for p in grid.patches], edges)
+    np.testing.assert_array_equal(hist, hist_o)
+    for g, w in zip(got, want):
+        assert (g["cells"], g["min"], g["max"]) == (w["cells"], w["min"], w["max"])
+        assert g["sum"] == pytest.approx(w["sum"], rel=1e-12)
+        assert g["sum_sq"] == pytest.approx(w["sum_sq"], rel=1e-12)
+    F = ndgp.total_force(grid, [dev(x) for x in phis], [dev(x) for x in psis])
+    for lvl in range(len(phis)):
+        Fo = G.total_force(phis[lvl], psis[lvl], grid.level_h(lvl), lvl == 0)
+        assert np.abs(F[lvl].cpu().numpy() - Fo).max() <= 1e-13 * np.abs(Fo).max()
+
+
 @pytest.mark.parametrize("m,depth,nu1,nu2,threshold", [
     (16, 2, 2, 2, None), (32, 2, 1, 2, None), (64, 1, 3, 3, None), (128, 1, 2, 1, None),
     (32, 2, 2, 3, 0.1), (64, 1, 2, 2, 0.1),
