@@ -1567,7 +1567,10 @@ void sweep_fused_tiles(const Level &L, const double *pin, double *pout, unsigned
 template <bool PRO, bool PER>
 void sweep_fused_layout(const Level &L, const double *pin, double *pout, unsigned *fallbacks,
                         const double *phi_c, const double *hat_c, hipStream_t st) {
-    if (fused_tz(L.n) == 32) // n >= 256: long z-chunks, the halo planes are a small share
+    if (PER && L.n >= 512) { // chunks of 64 planes still make four full rounds of workgroups:
+        if constexpr (PER)   // half the halo planes (1.0% of a 512^3 solve; 32 planes before)
+            sweep_fused_tiles<64, 16, 64, 512, PRO, PER>(L, pin, pout, fallbacks, phi_c, hat_c, st);
+    } else if (fused_tz(L.n) == 32) // n >= 256: long z-chunks, the halo planes are a small share
         sweep_fused_tiles<64, 16, 32, 512, PRO, PER>(L, pin, pout, fallbacks, phi_c, hat_c, st);
     else // 128^3: short chunks, two workgroups per CU (4 planes: 5% faster than 8)
         sweep_fused_tiles<64, 16, 4, 512, PRO, PER>(L, pin, pout, fallbacks, phi_c, hat_c, st);

@@ -308,6 +308,23 @@ def test_patch_bottom_bitwise_equal_per_level_launches(m, depth, cellwise):
         assert torch.equal(x, y)
 
 
+@pytest.mark.parametrize("precision", [ndgp.PREC_FP64, ndgp.PREC_MIXED])
+def test_sweep_of_64_plane_chunks_bitwise_equals_per_colour_launches(precision):
+    """512^3 levels are swept in z-chunks of 64 planes: the same bits, residuals and
+    events as one launch per colour, also where chunks meet and wrap."""
+    n = 512
+    f = synth.make_field(n // 4, 2.0, 53, n_tophats=10).delta
+    d = dev(f).repeat_interleave(4, 0).repeat_interleave(4, 1).repeat_interleave(4, 2).contiguous()
+    grid = ndgp.Grid(n=n, h=ndgp.cell_size(float(n), n))
+    p = dict(rc=1.0, tol=2e-2, precision=precision)
+    a, ra = ndgp.solve(grid, ndgp.Params(**p), [d])
+    b, rb = ndgp.solve(grid, ndgp.Params(two_pass=True, **p), [d])
+    torch.cuda.synchronize()
+    assert ra.status == rb.status == 0 and ra.history == rb.history
+    assert (ra.fallbacks, ra.holds) == (rb.fallbacks, rb.holds)
+    assert torch.equal(a[0], b[0])
+
+
 @pytest.mark.parametrize("nu1,nu2", [(1, 1), (3, 1), (1, 3)])
 def test_odd_sweep_counts(nu1, nu2):
     """Odd numbers of pre/post sweeps: the fused one-launch sweeps take the
