@@ -504,7 +504,7 @@ void ndgp_plan_destroy(ndgp_plan *plan);
  *                     depth by tree depth: ghost shell and initial guess
  *                     interpolated, then relaxed with its own FAS multigrid
  *                     (NDGP_MODE_FULL; boxes of at most 16^3 cells, and 32^3
- *                     ones when four or more share a depth, all in one launch
+ *                     ones when seven or more share a depth, all in one launch
  *                     of one workgroup each; the result is bit for bit that of
  *                     relaxing them one after the other, which NDGP_TWO_PASS
  *                     forces), or

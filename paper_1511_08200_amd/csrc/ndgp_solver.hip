@@ -1172,10 +1172,10 @@ size_t carve_amr(AmrScratch &A, char *base, int maxn, int nb = 0, int n32 = 0,
 
 // A relaxed box is solved by the one-workgroup kernel if it has at most 16^3
 // cells, or 32^3 when at least kBatch32Min boxes of that size share its tree
-// level: one workgroup relaxes a 32^3 box's two finer levels from L2, about
-// four times as slowly as the per-level launches do one box, so a few such
-// boxes go faster one after the other (measured: even at four).
-constexpr int kBatch32Min = 4;
+// level: one workgroup relaxes a 32^3 box's two finer levels from L2 in 5.0 ms
+// (up to 24 of them together in 5.7), the per-level launches do one box after
+// the other in 0.74 ms each (six 4.45 against 5.0 ms, eight 5.99 against 5.58).
+constexpr int kBatch32Min = 7;
 
 struct BatchPlan {
     int n32_at_depth[22] = {}; // relaxed 32^3 boxes per tree level

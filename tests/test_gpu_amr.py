@@ -202,3 +202,20 @@ def test_empty_tree_is_the_plain_solve():
     torch.cuda.synchronize()
     assert pa == [] and ra.cycles[0] == rb.cycles[0] and ra.rel_res[0] == rb.rel_res[0]
     assert torch.equal(a[0], b[0])
+
+
+@pytest.mark.parametrize("count", [6, 7])
+def test_few_32_boxes_on_a_level_equal_box_by_box(count):
+    """Six 32^3 boxes on a tree level are relaxed one after the other, seven in one
+    launch: both give the bits and reports of the per-colour box-by-box path."""
+    n, rng = 64, np.random.default_rng(60 + count)
+    grid = ndgp.Grid(n=n, h=1.0)
+    boxes = [ndgp.Box(-1, 32, (16 * (q % 4), 16 * (q // 4), 16 * (q % 3))) for q in range(count)]
+    d0 = rng.lognormal(0.0, 0.8, (n,) * 3)
+    dd = [dev(d0 - d0.mean())] + [dev(rng.lognormal(0.0, 0.8, (32,) * 3) - 1.3) for _ in boxes]
+    a, b = (ndgp.solve_amr(grid, ndgp.Params(rc=1.0, tol=1e-10, two_pass=t), boxes, dd)
+            for t in (False, True))
+    torch.cuda.synchronize()
+    assert a[1].status == b[1].status == 0 and a[2] == b[2]
+    assert (a[1].fallbacks, a[1].holds) == (b[1].fallbacks, b[1].holds)
+    assert all(torch.equal(x, y) for x, y in zip(a[0], b[0]))
