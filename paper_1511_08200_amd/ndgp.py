@@ -362,6 +362,20 @@ def workspace(nbytes: int, device=None, stream=None) -> torch.Tensor:
     return ws
 
 
+def _scratch(nbytes: int, device, stream):
+    """Scratch that one call may use: its own buffer, from the allocator's pool of
+    the stream the call enqueues on, so that it goes back when the call returns and
+    is handed out again only to work behind it (a captured call keeps it with its
+    graph).  None for no bytes, or where there is no room."""
+    if nbytes == 0:
+        return None
+    try:
+        with torch.cuda.stream(stream):
+            return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        return None
+
+
 def _arr3(ptrs):
     a = (ctypes.c_void_p * (1 + MAX_PATCHES))()
     for i, p in enumerate(ptrs):
@@ -693,7 +707,7 @@ def cic_force(grid: Grid, force: Sequence[torch.Tensor], pos: torch.Tensor, out=
             for l in range(1 + len(grid.patches))]
     # many particles: scratch that lets them read the components side by side
     nb = int(lib().ndgp_cic_force_workspace_bytes(ctypes.byref(g), npart))
-    ws = workspace(nb, pos.device, stream) if nb else None
+    ws = _scratch(nb, pos.device, stream)
     _check(lib().ndgp_cic_force_in(ctypes.byref(g), _arr3(fptr), _dev(pos, (3, npart), "pos"),
                                    npart, _dev(out, (3, npart), "out"),
                                    ws.data_ptr() if ws is not None else None,

@@ -2,6 +2,8 @@
 Sec. IV.A) against the CPU oracle (oracle/cic.py), through the C ABI."""
 from __future__ import annotations
 
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -147,6 +149,59 @@ def test_interleaved_gather_equals_component_gather(n, m, count, ordered):
     torch.cuda.synchronize()
     assert status == ndgp.NDGP_OK
     assert torch.equal(got, want)
+
+
+def _gather_case(n, count, seed):
+    """Particles in no order (the gather then uses its scratch) and a force field."""
+    rng = np.random.default_rng(seed)
+    grid = ndgp.Grid(n=n, h=1.0)
+    return grid, dev(rng.standard_normal((3, n, n, n))), dev(rng.random((3, count)))
+
+
+def test_two_threads_gather_on_one_stream():
+    """Two host threads that gather different forces on the default stream each get
+    the values of the call alone."""
+    cases = [_gather_case(64, 262144, s) for s in (1, 2)]
+    want = [ndgp.cic_force(g, [f], p) for g, f, p in cases]
+    torch.cuda.synchronize()
+    start, got = threading.Barrier(2), [[], []]
+
+    def work(i):
+        g, f, p = cases[i]
+        start.wait()
+        got[i] = [ndgp.cic_force(g, [f], p) for _ in range(20)]
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert all(len(got[i]) == 20 and all(torch.equal(x, want[i]) for x in got[i]) for i in range(2))
+
+
+def test_captured_gather_keeps_its_scratch():
+    """A captured gather replays right after a larger gather on its stream."""
+    grid, force, pos = _gather_case(64, 262144, 3)
+    large = _gather_case(128, 262144, 4)
+    want, want_large = ndgp.cic_force(grid, [force], pos), ndgp.cic_force(large[0], [large[1]], large[2])
+    side, out = torch.cuda.Stream(), torch.empty_like(pos)
+    side.wait_stream(torch.cuda.current_stream())
+    ndgp.cic_force(grid, [force], pos, out=out, stream=side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        ndgp.cic_force(grid, [force], pos, out=out, stream=side)
+    for _ in range(3):
+        got = ndgp.cic_force(large[0], [large[1]], large[2], stream=side)
+        torch.cuda.synchronize()
+        taken = [torch.full((1 << 20,), 7.0, dtype=torch.float64, device="cuda") for _ in range(24)]
+        out.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want) and torch.equal(got, want_large)
+        assert all(bool((t == 7.0).all()) for t in taken)
 
 
 def test_cic_rejects_bad_arguments():
