@@ -27,9 +27,10 @@ using namespace dev;
 constexpr double kCicOne = 68719476736.0; // 2^36: one particle in fixed point
 
 // w particles (0 <= w <= 1) in fixed point, rounded to nearest: adding 2^52 leaves
-// the rounded integer in the low mantissa bits (w 2^36 is far below 2^52)
+// the rounded integer in the low mantissa bits (w 2^36 is far below 2^52).  A weight
+// that is no number (the position was none) is nothing: the maximum is 2^52 then.
 __device__ __forceinline__ unsigned long long cic_fixed(double w) {
-    const double r = w * kCicOne + 0x1p52;
+    const double r = fmax(fma(w, kCicOne, 0x1p52), 0x1p52);
     return (unsigned long long)__double_as_longlong(r) & 0xfffffffffffffull;
 }
 

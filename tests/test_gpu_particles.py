@@ -151,6 +151,25 @@ def test_interleaved_gather_equals_component_gather(n, m, count, ordered):
     assert torch.equal(got, want)
 
 
+@pytest.mark.parametrize("count", [3000, 120000])  # direct atomics; sorted by tile
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), -float("inf")])
+def test_positions_that_are_no_numbers_add_nothing(count, bad):
+    """A particle with a coordinate that is no finite number counts in the mean and
+    adds to no cell, on the domain and on a patch."""
+    say(f"positions with {bad} among {count}")
+    rng = np.random.default_rng(count)
+    grid = ndgp.Grid(n=32, h=1.0, patches=[ndgp.Patch(32, (8, 8, 8))])
+    pos = rng.random((3, count))
+    odd = rng.random((3, 64))
+    for q in range(64):  # every set of axes
+        odd[[a for a in range(3) if (q % 7 + 1) >> a & 1], q] = bad
+    alone = ndgp.cic_density(grid, dev(pos))
+    got = ndgp.cic_density(grid, dev(np.concatenate([pos[:, :99], odd, pos[:, 99:]], axis=1)))
+    for a, g in zip(alone, got):  # delta + 1 = cells count / particles, rounded twice
+        want = (a + 1.0) * (count / (count + 64.0))
+        assert float((g + 1.0 - want).abs().max()) <= 1e-15 * (1.0 + float(want.max())) * 4
+
+
 def _gather_case(n, count, seed):
     """Particles in no order (the gather then uses its scratch) and a force field."""
     rng = np.random.default_rng(seed)
