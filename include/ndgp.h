@@ -394,7 +394,7 @@ ndgp_status ndgp_geff_stats(const ndgp_grid *grid, const double *const phi[1 + N
  *                     of force[l] (3 * cells(l), as ndgp_force or
  *                     ndgp_total_force write it) from the finest level whose
  *                     eight cells around the particle all lie inside it.
- *                     Enqueues only.
+ *                     out may be pos.  Enqueues only.
  */
 #define NDGP_CIC_MAX_PARTICLES (1LL << 28)
 /* Refinement criterion (Sec. IV.A): a cell is refined when the particles in

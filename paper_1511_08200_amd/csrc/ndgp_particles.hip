@@ -540,10 +540,10 @@ k_cic_interleave(const double *__restrict__ f, size_t cells, const unsigned *__r
     }
 }
 
-// `parts` consecutive components from `part` on of the finest level around a
-// particle; STRIDE of a cell's value: 1 in a component array, 3 interleaved
+// PARTS components at a particle from the cells of a level: STRIDE values from
+// cell to cell, `pitch` from component to component
 template <int PARTS, int STRIDE>
-__device__ __forceinline__ void cic_gather_cells(const double *__restrict__ f, int m, bool per,
+__device__ __forceinline__ void cic_gather_cells(const double *f, size_t pitch, int m, bool per,
                                                  int i0, int j0, int k0, double tx, double ty,
                                                  double tz, double acc[PARTS]) {
 #pragma unroll
@@ -564,8 +564,27 @@ __device__ __forceinline__ void cic_gather_cells(const double *__restrict__ f, i
                 }
                 const double *v = f + STRIDE * (((size_t)ck * m + cj) * m + ci);
 #pragma unroll
-                for (int a = 0; a < PARTS; ++a) acc[a] = fma(w, v[a], acc[a]);
+                for (int a = 0; a < PARTS; ++a) acc[a] = fma(w, v[a * pitch], acc[a]);
             }
+}
+
+// the finest level whose eight cells around the particle all lie inside it, their
+// lower cell and the weights
+__device__ __forceinline__ int cic_finest(const CicLevels &lv, double x, double y, double z,
+                                          int &i0, int &j0, int &k0, double &tx, double &ty,
+                                          double &tz) {
+    for (int q = lv.levels - 1; q > 0; --q) {
+        const int m = lv.m[q];
+        const double cpd = lv.cells_per_domain[q];
+        if (cic_inside(x, lv.n, lv.corner[q][0], cpd, m, false, i0, tx) &&
+            cic_inside(y, lv.n, lv.corner[q][1], cpd, m, false, j0, ty) &&
+            cic_inside(z, lv.n, lv.corner[q][2], cpd, m, false, k0, tz))
+            return q;
+    }
+    cic_inside(x, lv.n, lv.corner[0][0], 1.0, lv.n, true, i0, tx);
+    cic_inside(y, lv.n, lv.corner[0][1], 1.0, lv.n, true, j0, ty);
+    cic_inside(z, lv.n, lv.corner[0][2], 1.0, lv.n, true, k0, tz);
+    return 0;
 }
 
 __global__ void __launch_bounds__(kBlock)
@@ -576,30 +595,38 @@ k_cic_gather(const double *__restrict__ pos, long long np, unsigned blocks, CicL
     const long long p = (long long)(blockIdx.x - part * blocks) * kBlock + threadIdx.x;
     const bool together = lines && !*lines_off;
     if (p >= np) return;
-    const double x = pos[p], y = pos[np + p], z = pos[2 * np + p];
-    for (int q = lv.levels - 1; q >= 0; --q) {
-        const bool per = q == 0;
-        if (per && together && part > 0) return; // with the first component
-        const int m = lv.m[q];
-        const double cpd = lv.cells_per_domain[q];
-        int i0, j0, k0;
-        double tx, ty, tz;
-        if (!cic_inside(x, lv.n, lv.corner[q][0], cpd, m, per, i0, tx)) continue;
-        if (!cic_inside(y, lv.n, lv.corner[q][1], cpd, m, per, j0, ty)) continue;
-        if (!cic_inside(z, lv.n, lv.corner[q][2], cpd, m, per, k0, tz)) continue;
-        if (per && together) {
-            double acc[3];
-            cic_gather_cells<3, 3>(lines, m, true, i0, j0, k0, tx, ty, tz, acc);
+    if (together && part > 0 && lv.levels == 1) return; // with the first component
+    int i0, j0, k0;
+    double tx, ty, tz;
+    const int q = cic_finest(lv, pos[p], pos[np + p], pos[2 * np + p], i0, j0, k0, tx, ty, tz);
+    const int m = lv.m[q];
+    if (together && q == 0) {
+        if (part > 0) return;
+        double acc[3];
+        cic_gather_cells<3, 3>(lines, 1, m, true, i0, j0, k0, tx, ty, tz, acc);
 #pragma unroll
-            for (int a = 0; a < 3; ++a) out[a * np + p] = acc[a];
-        } else {
-            double acc[1];
-            cic_gather_cells<1, 1>(lv.force[q] + part * ((size_t)m * m * m), m, per, i0, j0, k0,
-                                   tx, ty, tz, acc);
-            out[part * np + p] = acc[0];
-        }
-        return;
+        for (int a = 0; a < 3; ++a) out[a * np + p] = acc[a];
+    } else {
+        double acc[1];
+        cic_gather_cells<1, 1>(lv.force[q] + part * ((size_t)m * m * m), 0, m, q == 0, i0, j0, k0,
+                               tx, ty, tz, acc);
+        out[part * np + p] = acc[0];
     }
+}
+
+// The same with all components of a particle in one thread, which reads the position
+// before it writes: for `out` over `pos`.
+__global__ void __launch_bounds__(kBlock)
+k_cic_gather_in_place(const double *pos, long long np, CicLevels lv, double *out) {
+    const long long p = (long long)blockIdx.x * kBlock + threadIdx.x;
+    if (p >= np) return;
+    int i0, j0, k0;
+    double tx, ty, tz, acc[3];
+    const int q = cic_finest(lv, pos[p], pos[np + p], pos[2 * np + p], i0, j0, k0, tx, ty, tz);
+    const int m = lv.m[q];
+    cic_gather_cells<3, 1>(lv.force[q], (size_t)m * m * m, m, q == 0, i0, j0, k0, tx, ty, tz, acc);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) out[a * np + p] = acc[a];
 }
 
 // Refinement criterion of Sec. IV.A: a cell is refined when the particles in
@@ -739,6 +766,10 @@ void launch_cic_gather(const double *pos, long long np, const CicLevels &lv, dou
                        unsigned *lines_off, double *out, hipStream_t st) {
     if (np <= 0) return;
     const unsigned nb = (unsigned)((np + kBlock - 1) / kBlock);
+    if (out < pos + 3 * np && pos < out + 3 * np) {
+        k_cic_gather_in_place<<<nb, kBlock, 0, st>>>(pos, np, lv, out);
+        return;
+    }
     if (lines) {
         const size_t cells = (size_t)lv.n * lv.n * lv.n;
         k_cic_probe_order<<<1, kBlock, 0, st>>>(pos, np, lv.n, lines_off);

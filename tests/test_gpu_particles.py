@@ -177,6 +177,24 @@ def _gather_case(n, count, seed):
     return grid, dev(rng.standard_normal((3, n, n, n))), dev(rng.random((3, count)))
 
 
+@pytest.mark.parametrize("n,m,count", [(32, 32, 3001), (64, 32, 600001), (128, 0, 1 << 20),
+                                       (256, 0, 1 << 21)])
+def test_gather_over_the_positions(n, m, count):
+    """out may be pos: the same bits as into a buffer of its own, for few particles and
+    for as many as have scratch."""
+    say(f"gather in place n={n} patch={m} particles={count}")
+    g = torch.Generator(device="cuda").manual_seed(count)
+    patches = [ndgp.Patch(m, (n - m // 4, -3, n // 2))] if m else []
+    grid = ndgp.Grid(n=n, h=1.0, patches=patches)
+    force = [torch.randn((3,) + (grid.level_n(l),) * 3, generator=g, device="cuda",
+                         dtype=torch.float64) for l in range(1 + len(patches))]
+    pos = torch.rand((3, count), generator=g, device="cuda", dtype=torch.float64)
+    want = ndgp.cic_force(grid, force, pos)
+    got = ndgp.cic_force(grid, force, pos, out=pos)
+    torch.cuda.synchronize()
+    assert got is pos and torch.equal(got, want)
+
+
 def test_two_threads_gather_on_one_stream():
     """Two host threads that gather different forces on the default stream each get
     the values of the call alone."""
