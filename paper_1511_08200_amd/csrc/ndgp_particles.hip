@@ -17,6 +17,7 @@
 
 #include "ndgp_device.h"
 
+#include <algorithm>
 #include <cmath>
 
 namespace ndgp {
@@ -498,45 +499,56 @@ __device__ __forceinline__ bool cic_inside(double x01, int n, double corner,
 // per particle, which the fabric delivers at 6 TB/s (9 TB/s where the three
 // components fit the 256 MB memory-side cache).
 //
-// One component per block, the blocks of the first component first: the lines in
-// flight then belong to one array, a third of the footprint, and a thread holds a
-// third of the sums (2^24 particles in no order on 128^3 / 256^3 / 512^3 cells 3.8
-// / 4.6 / 5.5 -> 2.9 / 3.9 / 4.2 ms; in cell order on 256^3 0.61 -> 0.50).
+// k_cic_gather_parts: one component per block, the blocks of the first component
+// first.  The lines in flight then belong to one array, a third of the footprint, and
+// a thread holds a third of the sums; the positions are read three times.
 //
-// With a workspace (`lines`) the domain's components are interleaved first, x y z
-// of a cell together: five lines instead of twelve, for one more pass over the
-// cells.  Particles in cell order touch few lines anyway, so a sample of
-// neighbouring particles decides on the device (*lines_off); the arithmetic is
-// the same.
-constexpr int kCicProbes = 1024;
-
+// With a workspace (`lines`) the domain's components may be interleaved first, x y z
+// of a cell together: five lines instead of twelve, for one more pass over the cells,
+// and k_cic_gather_cells takes the three sums of a particle in one thread.  With more
+// particles than cells that is the faster for particles in any order; with fewer, not
+// for those in cell order, which touch few lines anyway: there a sample of neighbouring
+// particles decides on the device (*lines_off), and one of the two kernels returns at
+// once.  The arithmetic is the same everywhere.
+//
+// 2^24 particles, us a call: one thread per particle on component arrays / one
+// component per block / interleaved
+//   no order    32^3 1560 / 926 / 562, 64^3 2130 / 1006 / 892, 128^3 3750 / 2930 / 1533,
+//               256^3 4270 / 3950 / 1837, 512^3 5440 / 4350 / 3500
+//   cell order  32^3 446 / 551 / 356, 128^3 443 / 556 / 387, 256^3 634 / 577 / 591,
+//               512^3 1490 / 1068 / 1950
+// Two cells per thread: 48 bytes in a row written (cells is a power of two, lines
+// 16-byte aligned).  ASK: not for particles in cell order, which every block finds out
+// from the same kBlock pairs of neighbouring particles (a launch less than asking
+// first), and the first one leaves in *lines_off.
+template <bool ASK>
 __global__ void __launch_bounds__(kBlock)
-k_cic_probe_order(const double *__restrict__ pos, long long np, int n,
-                  unsigned *__restrict__ lines_off) {
-    int near = 0;
-    for (int s = threadIdx.x; s < kCicProbes; s += kBlock) {
-        const long long p = (np - 1) * s / kCicProbes; // and p + 1 < np
-        const double reach[3] = {16.0, 2.0, 2.0};      // cells in x, y, z
-        bool ok = true;
+k_cic_interleave(const double *__restrict__ f, size_t cells, double *__restrict__ lines,
+                 const double *__restrict__ pos, long long np, int n,
+                 unsigned *__restrict__ lines_off) {
+    if constexpr (ASK) {
+        const long long p = (np - 1) * (int)threadIdx.x / kBlock; // and p + 1 < np
+        const double reach[3] = {16.0, 2.0, 2.0};                 // cells in x, y, z
+        bool near = true;
 #pragma unroll
         for (int a = 0; a < 3; ++a)
-            ok = ok && fabs(pos[a * np + p + 1] - pos[a * np + p]) * n <= reach[a];
-        near += ok ? 1 : 0;
+            near = near && fabs(pos[a * np + p + 1] - pos[a * np + p]) * n <= reach[a];
+        const bool off = 2 * __syncthreads_count(near) > kBlock;
+        if (blockIdx.x == 0 && threadIdx.x == 0) *lines_off = off ? 1u : 0u;
+        if (off) return;
     }
-    const double total = block_sum((double)near);
-    if (threadIdx.x == 0) *lines_off = 2.0 * total > (double)kCicProbes ? 1u : 0u;
-}
-
-__global__ void __launch_bounds__(kBlock)
-k_cic_interleave(const double *__restrict__ f, size_t cells, const unsigned *__restrict__ lines_off,
-                 double *__restrict__ lines) {
-    if (*lines_off) return;
-    for (size_t c = (size_t)blockIdx.x * kBlock + threadIdx.x; c < cells;
-         c += (size_t)gridDim.x * kBlock) {
-        const double x = f[c], y = f[cells + c], z = f[2 * cells + c];
-        lines[3 * c] = x;
-        lines[3 * c + 1] = y;
-        lines[3 * c + 2] = z;
+    for (size_t c = 2 * ((size_t)blockIdx.x * kBlock + threadIdx.x); c < cells;
+         c += 2 * (size_t)gridDim.x * kBlock) {
+        double v[6];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            v[a] = f[a * cells + c];
+            v[3 + a] = f[a * cells + c + 1];
+        }
+        double2 *o = reinterpret_cast<double2 *>(lines + 3 * c);
+        o[0] = make_double2(v[0], v[1]);
+        o[1] = make_double2(v[2], v[3]);
+        o[2] = make_double2(v[4], v[5]);
     }
 }
 
@@ -587,46 +599,48 @@ __device__ __forceinline__ int cic_finest(const CicLevels &lv, double x, double 
     return 0;
 }
 
+// with lines_off: only if it is set
 __global__ void __launch_bounds__(kBlock)
-k_cic_gather(const double *__restrict__ pos, long long np, unsigned blocks, CicLevels lv,
-             const double *__restrict__ lines, const unsigned *__restrict__ lines_off,
-             double *__restrict__ out) {
-    const int part = blockIdx.x / blocks;
-    const long long p = (long long)(blockIdx.x - part * blocks) * kBlock + threadIdx.x;
-    const bool together = lines && !*lines_off;
-    if (p >= np) return;
-    if (together && part > 0 && lv.levels == 1) return; // with the first component
-    int i0, j0, k0;
-    double tx, ty, tz;
-    const int q = cic_finest(lv, pos[p], pos[np + p], pos[2 * np + p], i0, j0, k0, tx, ty, tz);
-    const int m = lv.m[q];
-    if (together && q == 0) {
-        if (part > 0) return;
-        double acc[3];
-        cic_gather_cells<3, 3>(lines, 1, m, true, i0, j0, k0, tx, ty, tz, acc);
-#pragma unroll
-        for (int a = 0; a < 3; ++a) out[a * np + p] = acc[a];
-    } else {
-        double acc[1];
+k_cic_gather_parts(const double *__restrict__ pos, long long np, unsigned blocks, CicLevels lv,
+                   const unsigned *__restrict__ lines_off, double *__restrict__ out) {
+    if (lines_off && !*lines_off) return;
+    for (unsigned b = blockIdx.x; b < 3 * blocks; b += gridDim.x) {
+        const int part = b / blocks;
+        const long long p = (long long)(b - part * blocks) * kBlock + threadIdx.x;
+        if (p >= np) continue;
+        int i0, j0, k0;
+        double tx, ty, tz, acc[1];
+        const int q = cic_finest(lv, pos[p], pos[np + p], pos[2 * np + p], i0, j0, k0, tx, ty, tz);
+        const int m = lv.m[q];
         cic_gather_cells<1, 1>(lv.force[q] + part * ((size_t)m * m * m), 0, m, q == 0, i0, j0, k0,
                                tx, ty, tz, acc);
         out[part * np + p] = acc[0];
     }
 }
 
-// The same with all components of a particle in one thread, which reads the position
-// before it writes: for `out` over `pos`.
+// lines: the domain's components interleaved (null: they are not); with lines_off: only
+// if it is not set.  A particle's position is read before its sums are written, by the
+// same thread: `out` may be `pos`.
 __global__ void __launch_bounds__(kBlock)
-k_cic_gather_in_place(const double *pos, long long np, CicLevels lv, double *out) {
-    const long long p = (long long)blockIdx.x * kBlock + threadIdx.x;
-    if (p >= np) return;
-    int i0, j0, k0;
-    double tx, ty, tz, acc[3];
-    const int q = cic_finest(lv, pos[p], pos[np + p], pos[2 * np + p], i0, j0, k0, tx, ty, tz);
-    const int m = lv.m[q];
-    cic_gather_cells<3, 1>(lv.force[q], (size_t)m * m * m, m, q == 0, i0, j0, k0, tx, ty, tz, acc);
+k_cic_gather_cells(const double *pos, long long np, unsigned blocks, CicLevels lv,
+                   const double *__restrict__ lines, const unsigned *__restrict__ lines_off,
+                   double *out) {
+    if (lines_off && *lines_off) return;
+    for (unsigned b = blockIdx.x; b < blocks; b += gridDim.x) {
+        const long long p = (long long)b * kBlock + threadIdx.x;
+        if (p >= np) continue;
+        int i0, j0, k0;
+        double tx, ty, tz, acc[3];
+        const int q = cic_finest(lv, pos[p], pos[np + p], pos[2 * np + p], i0, j0, k0, tx, ty, tz);
+        const int m = lv.m[q];
+        if (lines && q == 0)
+            cic_gather_cells<3, 3>(lines, 1, m, true, i0, j0, k0, tx, ty, tz, acc);
+        else
+            cic_gather_cells<3, 1>(lv.force[q], (size_t)m * m * m, m, q == 0, i0, j0, k0, tx, ty,
+                                   tz, acc);
 #pragma unroll
-    for (int a = 0; a < 3; ++a) out[a * np + p] = acc[a];
+        for (int a = 0; a < 3; ++a) out[a * np + p] = acc[a];
+    }
 }
 
 // Refinement criterion of Sec. IV.A: a cell is refined when the particles in
@@ -756,26 +770,40 @@ void launch_cic_deposit(const double *pos, long long np, int n, const double cor
 }
 
 // Interleaving pays from about a particle per eight cells on (256^3 cells: 0.19 ms
-// for the pass, 0.12 ns less per particle), and not for so few that two more
-// launches count.
+// for the pass, 0.12 ns less per particle).  For few particles its launch counts:
+// 300000 of them on 64^3 cells take 49 us instead of 42 in no order and 35 instead of
+// 30 in cell order; 600000 64 instead of 61 and 42 instead of 40, on 32^3 45 instead of
+// 53 and 39 instead of 41, on 128^3 101 instead of 128 and 57 instead of 49.
 bool cic_gather_lines(long long np, int n) {
-    return np >= (1 << 18) && np >= (long long)((size_t)n * n * n / 8);
+    return np >= (1 << 19) && np >= (long long)((size_t)n * n * n / 8);
 }
 
 void launch_cic_gather(const double *pos, long long np, const CicLevels &lv, double *lines,
                        unsigned *lines_off, double *out, hipStream_t st) {
     if (np <= 0) return;
     const unsigned nb = (unsigned)((np + kBlock - 1) / kBlock);
-    if (out < pos + 3 * np && pos < out + 3 * np) {
-        k_cic_gather_in_place<<<nb, kBlock, 0, st>>>(pos, np, lv, out);
-        return;
-    }
+    const bool in_place = out < pos + 3 * np && pos < out + 3 * np;
+    const size_t cells = (size_t)lv.n * lv.n * lv.n;
+    const bool ask = lines && np <= (long long)cells && !in_place; // the device chooses
+    if (in_place && np <= (long long)cells) lines = nullptr;
     if (lines) {
-        const size_t cells = (size_t)lv.n * lv.n * lv.n;
-        k_cic_probe_order<<<1, kBlock, 0, st>>>(pos, np, lv.n, lines_off);
-        k_cic_interleave<<<kReduceBlocks, kBlock, 0, st>>>(lv.force[0], cells, lines_off, lines);
+        const unsigned ib = std::min((unsigned)kReduceBlocks / 2, blocks_for(cells / 2));
+        if (ask)
+            k_cic_interleave<true><<<ib, kBlock, 0, st>>>(lv.force[0], cells, lines, pos, np, lv.n,
+                                                         lines_off);
+        else
+            k_cic_interleave<false><<<ib, kBlock, 0, st>>>(lv.force[0], cells, lines, nullptr, 0,
+                                                          lv.n, nullptr);
     }
-    k_cic_gather<<<3 * nb, kBlock, 0, st>>>(pos, np, nb, lv, lines, lines_off, out);
+    // where one of two kernels returns at once, at most 65536 blocks do so (196608 idle
+    // ones take 80 us)
+    const unsigned cap = ask ? 65536 : ~0u;
+    if (ask || !(lines || in_place))
+        k_cic_gather_parts<<<std::min(3 * nb, cap), kBlock, 0, st>>>(pos, np, nb, lv,
+                                                                    ask ? lines_off : nullptr, out);
+    if (ask || lines || in_place)
+        k_cic_gather_cells<<<std::min(nb, cap), kBlock, 0, st>>>(pos, np, nb, lv, lines,
+                                                                ask ? lines_off : nullptr, out);
 }
 
 } // namespace ndgp

@@ -10,6 +10,7 @@ one-cell ghost shell, shape (m+2, m+2, m+2).
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import math
 import dataclasses
@@ -370,7 +371,7 @@ def _scratch(nbytes: int, device, stream):
     if nbytes == 0:
         return None
     try:
-        with torch.cuda.stream(stream):
+        with torch.cuda.stream(stream) if stream is not None else contextlib.nullcontext():
             return torch.empty(nbytes, dtype=torch.uint8, device=device)
     except torch.OutOfMemoryError:
         return None

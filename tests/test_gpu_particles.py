@@ -177,6 +177,36 @@ def _gather_case(n, count, seed):
     return grid, dev(rng.standard_normal((3, n, n, n))), dev(rng.random((3, count)))
 
 
+@pytest.mark.parametrize("n,m,count,ordered", [
+    (8, 0, 1 << 19, False),          # the smallest domain, the fewest particles with scratch
+    (32, 64, (1 << 19) + 1, True),   # a patch as wide as the domain
+    (128, 64, (1 << 19) - 1, False),  # too few
+    (128, 64, 600001, False),
+    (256, 0, 1 << 21, False),        # from here on the particles' order decides
+    (256, 128, (1 << 21) + 5, True),
+    (256, 128, 6000001, False),      # more particles than one round of blocks takes
+])
+def test_gather_routes_agree(n, m, count, ordered):
+    """Every route of the gather gives the bits of the one without scratch."""
+    say(f"gather routes n={n} patch={m} particles={count} ordered={ordered}")
+    g = torch.Generator(device="cuda").manual_seed(count)
+    patches = [ndgp.Patch(m, (n - m // 4, -3, n // 2))] if m else []
+    grid = ndgp.Grid(n=n, h=1.0, patches=patches)
+    force = [torch.randn((3,) + (grid.level_n(l),) * 3, generator=g, device="cuda",
+                         dtype=torch.float64) for l in range(1 + len(patches))]
+    pos = torch.rand((3, count), generator=g, device="cuda", dtype=torch.float64)
+    if ordered:
+        cell = (pos * n).long()
+        pos = pos[:, torch.argsort((cell[2] * n + cell[1]) * n + cell[0])].contiguous()
+    got = ndgp.cic_force(grid, force, pos)
+    want = torch.full_like(got, float("nan"))
+    status = ndgp.lib().ndgp_cic_force(grid._c(), ndgp._arr3([x.data_ptr() for x in force]),
+                                       pos.data_ptr(), count, want.data_ptr(), ndgp._stream(None))
+    torch.cuda.synchronize()
+    assert status == ndgp.NDGP_OK
+    assert torch.equal(got, want)
+
+
 @pytest.mark.parametrize("n,m,count", [(32, 32, 3001), (64, 32, 600001), (128, 0, 1 << 20),
                                        (256, 0, 1 << 21)])
 def test_gather_over_the_positions(n, m, count):
@@ -198,7 +228,7 @@ def test_gather_over_the_positions(n, m, count):
 def test_two_threads_gather_on_one_stream():
     """Two host threads that gather different forces on the default stream each get
     the values of the call alone."""
-    cases = [_gather_case(64, 262144, s) for s in (1, 2)]
+    cases = [_gather_case(64, 1 << 19, s) for s in (1, 2)]
     want = [ndgp.cic_force(g, [f], p) for g, f, p in cases]
     torch.cuda.synchronize()
     start, got = threading.Barrier(2), [[], []]
@@ -219,8 +249,8 @@ def test_two_threads_gather_on_one_stream():
 
 def test_captured_gather_keeps_its_scratch():
     """A captured gather replays right after a larger gather on its stream."""
-    grid, force, pos = _gather_case(64, 262144, 3)
-    large = _gather_case(128, 262144, 4)
+    grid, force, pos = _gather_case(64, 1 << 19, 3)
+    large = _gather_case(128, 1 << 19, 4)
     want, want_large = ndgp.cic_force(grid, [force], pos), ndgp.cic_force(large[0], [large[1]], large[2])
     side, out = torch.cuda.Stream(), torch.empty_like(pos)
     side.wait_stream(torch.cuda.current_stream())
