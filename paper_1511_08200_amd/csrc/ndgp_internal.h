@@ -390,12 +390,15 @@ size_t cic_segments(int m, size_t chunk);
 size_t cic_chunk(int n);
 // 64-bit words of a level's accumulators and tile counters
 size_t cic_acc_words(int m);
+// which of a grid's levels (m cells per side; 0 the domain) np particles are sorted on
+void cic_sorted_levels(const int *m, int levels, long long np, bool *sorted);
 void launch_zero_words(unsigned long long *a, size_t count, hipStream_t st);
 // Cloud-in-cell deposit of np particles (pos: x, y, z arrays of np doubles
 // each, box units) onto one level: m^3 cells of 2^-q domain cells with lower
 // corner `corner` (domain cells); q = 0 is the periodic domain (m = n).
 // acc: cic_acc_words(m) words (m^3 fixed-point accumulators first; only those
-// without scratch), zero on entry; delta = count / mean - 1.
+// without scratch), zero on entry; delta = count / mean - 1.  scr: sorted with it, or
+// empty.
 void launch_cic_deposit(const double *pos, long long np, int n, const double corner[3], int q,
                         int m, unsigned long long *acc, double *delta, const CicScratch &scr,
                         hipStream_t st);

@@ -703,13 +703,29 @@ size_t cic_acc_words(int m) {
     return (size_t)m * m * m + ((size_t)cic_bins(m) + 1) / 2; // then one 32-bit counter per tile
 }
 
-// From how many particles on the deposit is binned: below, its extra launches and
-// the tiles it writes cost more than the atomics they save.  Measured (particles in
-// no order; direct / binned, us): 32^3 cells 35 / 39 at 32768 and 58 / 31 at
-// 65536; 128^3 42 / 47 at 65536 and 67 / 50 at 131072; 256^3 113 / 140 at 131072,
-// 159 / 147 at 262144 and 5856 / 855 at 2^24; 512^3 960 / 1183 at 2^20 and 2079 /
-// 1459 at 2^22.
-static long long cic_binned_min(size_t cells) { return 49152 + (long long)(cells / 64); }
+// From how many particles on sorting a level pays: below, its extra launches and the
+// tiles it writes cost more than the atomics it saves.  Measured (particles in no order,
+// on a domain; direct / binned, us): 32^3 cells 35 / 39 at 32768 and 58 / 31 at 65536;
+// 128^3 42 / 47 at 65536 and 67 / 50 at 131072; 256^3 113 / 140 at 131072, 159 / 147 at
+// 262144 and 5856 / 855 at 2^24; 512^3 960 / 1183 at 2^20 and 2079 / 1459 at 2^22.
+//
+// On a refinement it saves what the particles inside cost, which is not known before
+// they have been looked at: 20 us at 32^3 and 64^3 cells, 30 at 128^3 and 85 at 256^3
+// go, whether few of them meet it (64^3 in 256^3, 300000 in no order: 228 us for both
+// levels instead of 208) or most of a dense field (32^3 in 64^3, as many: 112 instead
+// of 216).  So a refinement is sorted from the sum of all levels' lines on: what its
+// sort may cost is then saved already on the levels above (0.3 ns per particle beyond
+// their lines).
+static long long cic_sort_line(int m) {
+    return 49152 + (long long)((size_t)m * m * m / 64);
+}
+
+void cic_sorted_levels(const int *m, int levels, long long np, bool *sorted) {
+    long long all = 0;
+    for (int l = 0; l < levels; ++l) all += cic_sort_line(m[l]);
+    for (int l = 0; l < levels; ++l)
+        sorted[l] = cic_bins(m[l]) > 0 && np >= (l == 0 ? cic_sort_line(m[0]) : all);
+}
 
 void launch_zero_words(unsigned long long *a, size_t count, hipStream_t st) {
     k_zero_acc<<<blocks_for(count), kBlock, 0, st>>>(a, count);
@@ -755,11 +771,10 @@ void launch_cic_deposit(const double *pos, long long np, int n, const double cor
                         int m, unsigned long long *acc, double *delta, const CicScratch &scr,
                         hipStream_t st) {
     const size_t cells = (size_t)m * m * m;
-    const bool binned = scr.sorted && cic_bins(m) > 0 && np >= cic_binned_min(cells);
     const CicLevel L{n, corner[0], corner[1], corner[2], std::ldexp(1.0, q), m, q == 0 ? 1 : 0};
-    if (binned && q == 0)
+    if (scr.sorted && q == 0)
         cic_binned<kCicPeriodic>(pos, np, L, acc, scr, st);
-    else if (binned)
+    else if (scr.sorted)
         cic_binned<kCicPatch>(pos, np, L, acc, scr, st);
     else if (np > 0) // one kernel for every level: few particles are bound by its first fetch
         k_cic_deposit<<<(unsigned)((np + kBlock - 1) / kBlock), kBlock, 0, st>>>(pos, np, L, acc);

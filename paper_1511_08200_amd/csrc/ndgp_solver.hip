@@ -1655,14 +1655,16 @@ ndgp_status cic_density_impl(const ndgp_grid *grid, const double *pos, int64_t n
     unsigned long long *acc[1 + NDGP_MAX_PATCHES];
     CicScratch scr;
     carve_cic(c, aligned_base(ws), plain, acc, &scr);
+    int m[1 + NDGP_MAX_PATCHES];
+    bool sorted[1 + NDGP_MAX_PATCHES];
+    for (int l = 0; l <= c.np; ++l) m[l] = c.nlev(l);
+    cic_sorted_levels(m, c.np + 1, (long long)np, sorted);
+    auto words = [&](int l) { return plain ? (size_t)m[l] * m[l] * m[l] : cic_acc_words(m[l]); };
     // the levels' accumulators lie one after the other: cleared together
-    const size_t last = (size_t)c.nlev(c.np);
-    launch_zero_words(acc[0], (size_t)(acc[c.np] - acc[0]) +
-                                  (plain ? last * last * last : cic_acc_words(c.nlev(c.np))),
-                      st);
+    launch_zero_words(acc[0], (size_t)(acc[c.np] - acc[0]) + words(c.np), st);
     for (int l = 0; l <= c.np; ++l)
-        launch_cic_deposit(pos, (long long)np, c.n, corner[l], l, c.nlev(l), acc[l], delta[l],
-                           scr, st);
+        launch_cic_deposit(pos, (long long)np, c.n, corner[l], l, m[l], acc[l], delta[l],
+                           sorted[l] ? scr : CicScratch{}, st);
     HIP_TRY(hipGetLastError());
     return NDGP_OK;
 }

@@ -170,6 +170,27 @@ def test_positions_that_are_no_numbers_add_nothing(count, bad):
         assert float((g + 1.0 - want).abs().max()) <= 1e-15 * (1.0 + float(want.max())) * 4
 
 
+@pytest.mark.parametrize("n,ms,count", [
+    (32, (32,), 99327), (32, (32,), 99328),           # the sum of the levels' lines
+    (64, (32, 32), 152575), (64, (32, 32), 152576),
+    (256, (128,), 320001),                            # the domain sorted, the patch not
+])
+def test_deposit_levels_sorted_or_not_agree(n, ms, count):
+    """Levels sorted by tile and levels that are not, in one call: the bits of direct
+    atomics on every level."""
+    say(f"deposit lines n={n} patches={ms} particles={count}")
+    g = torch.Generator(device="cuda").manual_seed(count)
+    pos = torch.rand((3, count), generator=g, device="cuda", dtype=torch.float64)
+    patches = [ndgp.Patch(m, (2, 3, 2)) for m in ms]
+    grid = ndgp.Grid(n=n, h=1.0, patches=patches)
+    plain = 8 * (n**3 + sum(m**3 for m in ms)) + 4096  # room for guard bands
+    direct = ndgp.cic_density(grid, pos, ws=torch.empty(plain, dtype=torch.uint8, device="cuda"))
+    got = ndgp.cic_density(grid, pos)
+    torch.cuda.synchronize()
+    for a, b in zip(got, direct):
+        assert torch.equal(a, b)
+
+
 def _gather_case(n, count, seed):
     """Particles in no order (the gather then uses its scratch) and a force field."""
     rng = np.random.default_rng(seed)
