@@ -1660,11 +1660,18 @@ ndgp_status cic_density_impl(const ndgp_grid *grid, const double *pos, int64_t n
     for (int l = 0; l <= c.np; ++l) m[l] = c.nlev(l);
     cic_sorted_levels(m, c.np + 1, (long long)np, sorted);
     auto words = [&](int l) { return plain ? (size_t)m[l] * m[l] * m[l] : cic_acc_words(m[l]); };
-    // the levels' accumulators lie one after the other: cleared together
-    launch_zero_words(acc[0], (size_t)(acc[c.np] - acc[0]) + words(c.np), st);
-    for (int l = 0; l <= c.np; ++l)
+    // The levels' accumulators lie one after the other.  Small ones are cleared together
+    // (a launch per level less); more than a quarter of the 256 MB memory-side cache
+    // level by level, so that each level's are still there when its density is formed
+    // (two levels of 256^3, 50000 particles: 182 us, together 207).
+    const size_t all = (size_t)(acc[c.np] - acc[0]) + words(c.np);
+    const bool together = all * sizeof(*acc[0]) <= (size_t)64 << 20;
+    if (together) launch_zero_words(acc[0], all, st);
+    for (int l = 0; l <= c.np; ++l) {
+        if (!together) launch_zero_words(acc[l], words(l), st);
         launch_cic_deposit(pos, (long long)np, c.n, corner[l], l, m[l], acc[l], delta[l],
                            sorted[l] ? scr : CicScratch{}, st);
+    }
     HIP_TRY(hipGetLastError());
     return NDGP_OK;
 }

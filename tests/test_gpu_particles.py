@@ -174,6 +174,7 @@ def test_positions_that_are_no_numbers_add_nothing(count, bad):
     (32, (32,), 99327), (32, (32,), 99328),           # the sum of the levels' lines
     (64, (32, 32), 152575), (64, (32, 32), 152576),
     (256, (128,), 320001),                            # the domain sorted, the patch not
+    (256, (128, 64), 3001),                           # levels cleared one by one
 ])
 def test_deposit_levels_sorted_or_not_agree(n, ms, count):
     """Levels sorted by tile and levels that are not, in one call: the bits of direct
