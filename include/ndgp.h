@@ -385,11 +385,12 @@ ndgp_status ndgp_geff_stats(const ndgp_grid *grid, const double *const phi[1 + N
  *                     64-bit fixed-point numbers (2^-36 of a particle), so the
  *                     result is the same bits on every run.  1 <= N <=
  *                     NDGP_CIC_MAX_PARTICLES.  Workspace:
- *                     ndgp_cic_workspace_bytes(grid): 8 bytes per cell of
- *                     every level, and scratch to sort the particles by tile
- *                     (a workspace without room for that scratch is accepted;
- *                     the deposit then is slower, with the same bits).
- *                     Enqueues only.
+ *                     ndgp_cic_density_workspace_bytes(grid, N): 8 bytes per
+ *                     cell of every level, and where N is large enough scratch
+ *                     to sort the particles by tile (a workspace without room
+ *                     for that scratch is accepted; the deposit then is slower,
+ *                     with the same bits).  ndgp_cic_workspace_bytes(grid) is
+ *                     enough for any N.  Enqueues only.
  * ndgp_cic_force      out (3 * N, x then y then z) = cloud-in-cell interpolation
  *                     of force[l] (3 * cells(l), as ndgp_force or
  *                     ndgp_total_force write it) from the finest level whose
@@ -409,6 +410,7 @@ ndgp_status ndgp_refine_flags(const ndgp_grid *grid, const double *const delta[1
                               int64_t n_flagged[1 + NDGP_MAX_PATCHES], void *workspace,
                               size_t workspace_bytes, hipStream_t stream);
 size_t ndgp_cic_workspace_bytes(const ndgp_grid *grid);
+size_t ndgp_cic_density_workspace_bytes(const ndgp_grid *grid, int64_t n_particles);
 ndgp_status ndgp_cic_density(const ndgp_grid *grid, const double *pos, int64_t n_particles,
                              double *const delta[1 + NDGP_MAX_PATCHES], void *workspace,
                              size_t workspace_bytes, hipStream_t stream);

@@ -1604,24 +1604,35 @@ void level_corners(const Cfg &c, double corner[][3]) {
             corner[q + 1][a] = corner[q][a] + std::ldexp((double)c.po[q][a], -q);
 }
 
+// which levels np particles are sorted on; true if any
+bool cic_sorted(const Cfg &c, int64_t np, bool sorted[1 + NDGP_MAX_PATCHES]) {
+    int m[1 + NDGP_MAX_PATCHES];
+    for (int l = 0; l <= c.np; ++l) m[l] = c.nlev(l);
+    cic_sorted_levels(m, c.np + 1, (long long)np, sorted);
+    return std::any_of(sorted, sorted + c.np + 1, [](bool b) { return b; });
+}
+
 // The deposit's workspace: every level's accumulators, then the scratch of the
 // particle sort (one level at a time, so sized for the level that needs most).
-// A workspace that holds the accumulators alone (`plain`) is accepted: the
-// deposit then sends every particle's atomics to memory.
-size_t carve_cic(const Cfg &c, char *base, bool plain, unsigned long long **acc,
+// Where no level is sorted, or the workspace holds the accumulators alone
+// (`plain`), the deposit sends every particle's atomics to memory.
+size_t carve_cic(const Cfg &c, int64_t np, char *base, bool plain, unsigned long long **acc,
                  CicScratch *scr) {
     Carver cv{base};
+    bool sorted[1 + NDGP_MAX_PATCHES];
+    if (!cic_sorted(c, np, sorted)) plain = true;
     size_t bins = 0, segments = 0;
-    const size_t chunk = cic_chunk(c.n);
+    const size_t chunk = std::min(cic_chunk(c.n), (size_t)np);
     for (int l = 0; l <= c.np; ++l) {
         const int m = c.nlev(l);
         unsigned long long *a = cv.take<unsigned long long>(plain ? (size_t)m * m * m
                                                                   : cic_acc_words(m));
         if (acc) acc[l] = a;
+        if (!sorted[l]) continue;
         bins = std::max(bins, (size_t)cic_bins(m));
         segments = std::max(segments, cic_segments(m, chunk));
     }
-    if (!plain && bins > 0) {
+    if (!plain) {
         CicScratch s;
         s.chunk = chunk;
         s.sorted = cv.take<double>(3 * chunk);
@@ -1634,7 +1645,9 @@ size_t carve_cic(const Cfg &c, char *base, bool plain, unsigned long long **acc,
     return cv.off + 256;
 }
 
-size_t cic_bytes(const Cfg &c) { return carve_cic(c, nullptr, false, nullptr, nullptr); }
+size_t cic_bytes(const Cfg &c, int64_t np) {
+    return carve_cic(c, np, nullptr, false, nullptr, nullptr);
+}
 
 ndgp_status cic_density_impl(const ndgp_grid *grid, const double *pos, int64_t np,
                              double *const delta[], void *ws, size_t ws_bytes, hipStream_t st) {
@@ -1646,20 +1659,22 @@ ndgp_status cic_density_impl(const ndgp_grid *grid, const double *pos, int64_t n
         return fail(NDGP_EINVAL, "n_particles must be in [1, NDGP_CIC_MAX_PARTICLES]");
     for (int l = 0; l <= c.np; ++l)
         if (!delta[l]) return fail(NDGP_EINVAL, "delta of every level must not be NULL");
-    const bool plain = ws_bytes < cic_bytes(c);
-    if (!ws || ws_bytes < carve_cic(c, nullptr, true, nullptr, nullptr))
-        return fail(NDGP_ENOMEM, "workspace smaller than ndgp_cic_workspace_bytes() = " +
-                                     std::to_string(cic_bytes(c)));
+    bool sorted[1 + NDGP_MAX_PATCHES];
+    const bool plain = !cic_sorted(c, np, sorted) || ws_bytes < cic_bytes(c, np);
+    const size_t least = carve_cic(c, np, nullptr, true, nullptr, nullptr);
+    if (!ws || ws_bytes < least)
+        return fail(NDGP_ENOMEM, "workspace smaller than the accumulators' " +
+                                     std::to_string(least) +
+                                     " bytes (ndgp_cic_density_workspace_bytes)");
     double corner[1 + NDGP_MAX_PATCHES][3];
     level_corners(c, corner);
     unsigned long long *acc[1 + NDGP_MAX_PATCHES];
     CicScratch scr;
-    carve_cic(c, aligned_base(ws), plain, acc, &scr);
-    int m[1 + NDGP_MAX_PATCHES];
-    bool sorted[1 + NDGP_MAX_PATCHES];
-    for (int l = 0; l <= c.np; ++l) m[l] = c.nlev(l);
-    cic_sorted_levels(m, c.np + 1, (long long)np, sorted);
-    auto words = [&](int l) { return plain ? (size_t)m[l] * m[l] * m[l] : cic_acc_words(m[l]); };
+    carve_cic(c, np, aligned_base(ws), plain, acc, &scr);
+    auto words = [&](int l) {
+        const size_t m = (size_t)c.nlev(l);
+        return plain ? m * m * m : cic_acc_words((int)m);
+    };
     // The levels' accumulators lie one after the other.  Small ones are cleared together
     // (a launch per level less); more than a quarter of the 256 MB memory-side cache
     // level by level, so that each level's are still there when its density is formed
@@ -1669,7 +1684,7 @@ ndgp_status cic_density_impl(const ndgp_grid *grid, const double *pos, int64_t n
     if (together) launch_zero_words(acc[0], all, st);
     for (int l = 0; l <= c.np; ++l) {
         if (!together) launch_zero_words(acc[l], words(l), st);
-        launch_cic_deposit(pos, (long long)np, c.n, corner[l], l, m[l], acc[l], delta[l],
+        launch_cic_deposit(pos, (long long)np, c.n, corner[l], l, c.nlev(l), acc[l], delta[l],
                            sorted[l] ? scr : CicScratch{}, st);
     }
     HIP_TRY(hipGetLastError());
@@ -2055,13 +2070,18 @@ ndgp_status ndgp_solve(const ndgp_grid *grid, const ndgp_params *params,
 }
 
 size_t ndgp_cic_workspace_bytes(const ndgp_grid *grid) {
+    return ndgp_cic_density_workspace_bytes(grid, NDGP_CIC_MAX_PARTICLES);
+}
+
+size_t ndgp_cic_density_workspace_bytes(const ndgp_grid *grid, int64_t n_particles) {
     Cfg c;
     std::string why;
     if (!resolve_grid(grid, c, why)) {
         g_err = why;
         return 0;
     }
-    return cic_bytes(c);
+    const int64_t most = NDGP_CIC_MAX_PARTICLES;
+    return cic_bytes(c, std::clamp<int64_t>(n_particles, 1, most));
 }
 
 ndgp_status ndgp_cic_density(const ndgp_grid *grid, const double *pos, int64_t n_particles,

@@ -119,6 +119,8 @@ def lib():
                                           ctypes.POINTER(_Report)]
         L.ndgp_cic_workspace_bytes.restype = ctypes.c_size_t
         L.ndgp_cic_workspace_bytes.argtypes = [ctypes.POINTER(_Grid)]
+        L.ndgp_cic_density_workspace_bytes.restype = ctypes.c_size_t
+        L.ndgp_cic_density_workspace_bytes.argtypes = [ctypes.POINTER(_Grid), ctypes.c_int64]
         L.ndgp_cic_density.restype = ctypes.c_int
         L.ndgp_cic_density.argtypes = [ctypes.POINTER(_Grid), vp, ctypes.c_int64, arr3, vp,
                                        ctypes.c_size_t, vp]
@@ -570,7 +572,7 @@ def cic_density(grid: Grid, pos: torch.Tensor, delta=None, ws=None, stream=None)
                  for l in range(1 + len(grid.patches))]
     dptr = [_dev(delta[l], (grid.level_n(l),) * 3, f"delta[{l}]")
             for l in range(1 + len(grid.patches))]
-    nb = int(lib().ndgp_cic_workspace_bytes(ctypes.byref(g)))
+    nb = int(lib().ndgp_cic_density_workspace_bytes(ctypes.byref(g), npart))
     if nb == 0:
         _check(NDGP_EINVAL)
     if ws is None:

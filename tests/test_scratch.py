@@ -67,3 +67,38 @@ def test_cic_force_runs_without_room_for_scratch(on_host):
     on_host.setattr(torch, "empty", no_room)
     _call()
     assert lib.calls == [(None, 0)]
+
+
+class Density:
+    """The library's sizes, and a deposit that only looks at its workspace."""
+
+    def __init__(self):
+        self.library, self.held = ndgp.lib(), None
+
+    def __getattr__(self, name):
+        return getattr(self.library, name)
+
+    def ndgp_cic_density(self, grid, pos, count, delta, ws, ws_bytes, stream):
+        self.held = ws_bytes
+        return ndgp.NDGP_OK
+
+
+@pytest.mark.parametrize("n,m,count,extra", [
+    (256, 0, 1000, 0), (32, 32, 1000, 0), (256, 128, 311295, 0),  # no level sorted
+    (32, 0, 60000, 24 * 60000 + (1 << 19)),  # sorted: the particles, a table of 64 tiles
+    (64, 32, 1 << 26, (24 << 20) + (1 << 22)),  # a chunk of them at a time
+])
+def test_cic_density_holds_the_scratch_it_can_use(on_host, n, m, count, extra):
+    """The workspace of a deposit: the accumulators, and scratch for as many particles
+    as are sorted (guard bands and alignment of seven buffers aside)."""
+    lib = Density()
+    on_host.setattr(ndgp, "lib", lambda: lib)
+    grid = ndgp.Grid(n=n, h=1.0, patches=[ndgp.Patch(m, (2, 2, 2))] if m else [])
+    pos = torch.empty((3, count), dtype=torch.float64, device="meta")
+    on_host.setattr(ndgp, "_dev", lambda t, shape=None, name="": 0)
+    delta = [torch.empty(1, dtype=torch.float64)] * (2 if m else 1)
+    on_host.setattr(ndgp, "workspace", lambda nbytes, device, stream: torch.empty(nbytes, dtype=torch.uint8))
+    ndgp.cic_density(grid, pos, delta=delta)
+    least = 8 * (n**3 + m**3)
+    assert least <= lib.held <= least + extra + 7 * 1024
+    assert lib.held <= lib.library.ndgp_cic_workspace_bytes(grid._c())
