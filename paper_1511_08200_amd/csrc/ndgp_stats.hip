@@ -17,11 +17,14 @@ namespace {
 
 using namespace dev;
 
-// Bound by memory: two fields read, three written past the caches (nobody reads them
-// before a gigabyte of other traffic), which leaves the Infinity Cache to the fields'
-// neighbour planes.  256^3: 203 us with ordinary stores, 180 us now, 3.7 TB/s.  (Both
+// Bound by memory: two fields read, three written.  PAST: written past the caches, which
+// leaves them to the fields' neighbour planes; taken where the force is larger than the
+// 256 MB memory-side cache (from 256^3 on), so that whoever reads it next would not find
+// it there.  us, ordinary / past: 256^3 212 / 189, with ndgp_cic_force at 2^24
+// particles and ndgp_geff_stats behind it 2253 / 2206; 128^3 39.2 / 39.0 alone, but 44
+// / 48 with a gather of 1000 particles and 61 / 63 with one of 100000.  (256^3, both
 // fields streamed through LDS as k_force_tiled does, ordinary stores: 219 us.)
-template <bool PER>
+template <bool PER, bool PAST>
 __global__ void __launch_bounds__(kBlock)
 k_total_force(const double *__restrict__ phi, const double *__restrict__ psi, Ix<PER> ix,
               double c2h, double c4h, double *__restrict__ f) {
@@ -33,10 +36,11 @@ k_total_force(const double *__restrict__ phi, const double *__restrict__ psi, Ix
     const int up[3] = {ix(i + 1, j, k), ix(i, j + 1, k), ix(i, j, k + 1)};
     const int dn[3] = {ix(i - 1, j, k), ix(i, j - 1, k), ix(i, j, k - 1)};
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
-        __builtin_nontemporal_store(
-            -((psi[up[a]] - psi[dn[a]]) * c2h) - (phi[up[a]] - phi[dn[a]]) * c4h,
-            f + (size_t)a * cells + t);
+    for (int a = 0; a < 3; ++a) {
+        const double F = -((psi[up[a]] - psi[dn[a]]) * c2h) - (phi[up[a]] - phi[dn[a]]) * c4h;
+        if constexpr (PAST) __builtin_nontemporal_store(F, f + (size_t)a * cells + t);
+        else f[(size_t)a * cells + t] = F;
+    }
 }
 
 // G_eff - 1 of one cell: |F_5th| / |F_GR| = sqrt(sum dphi^2 / sum dpsi^2) / 2
@@ -198,12 +202,17 @@ void launch_total_force(const double *phi, const double *psi, int n, bool period
                         double *f, hipStream_t st) {
     const unsigned nb = blocks_for((size_t)n * n * n);
     const int lg = log2i(n);
-    if (periodic)
-        k_total_force<true><<<nb, kBlock, 0, st>>>(phi, psi, make_ix<true>(n, lg), 0.5 / h,
-                                                   0.25 / h, f);
-    else
-        k_total_force<false><<<nb, kBlock, 0, st>>>(phi, psi, make_ix<false>(n, lg), 0.5 / h,
-                                                    0.25 / h, f);
+    const bool past = n >= 256;
+    const double c2h = 0.5 / h, c4h = 0.25 / h;
+    if (periodic) {
+        const Ix<true> ix = make_ix<true>(n, lg);
+        if (past) k_total_force<true, true><<<nb, kBlock, 0, st>>>(phi, psi, ix, c2h, c4h, f);
+        else k_total_force<true, false><<<nb, kBlock, 0, st>>>(phi, psi, ix, c2h, c4h, f);
+    } else {
+        const Ix<false> ix = make_ix<false>(n, lg);
+        if (past) k_total_force<false, true><<<nb, kBlock, 0, st>>>(phi, psi, ix, c2h, c4h, f);
+        else k_total_force<false, false><<<nb, kBlock, 0, st>>>(phi, psi, ix, c2h, c4h, f);
+    }
 }
 
 void launch_geff_level(const double *phi, const double *psi, int n, bool periodic,

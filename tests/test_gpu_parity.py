@@ -690,6 +690,26 @@ def test_total_force_and_geff_stats_match_oracle():
         ndgp.geff_stats(grid, [dev(x) for x in phis], [dev(x) for x in psis], edges[::-1])
 
 
+@pytest.mark.parametrize("n,m", [(128, 256), (256, 128)])
+def test_total_force_large_and_small_levels(n, m):
+    """Levels whose force is written past the caches (256^3) and levels whose force is
+    not, periodic and padded: central differences of both potentials in FP64."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    grid = ndgp.Grid(n=n, h=0.5, patches=[ndgp.Patch(m, (0, 0, 0))])
+    phi, psi = ([torch.randn((s,) * 3, generator=g, device="cuda", dtype=torch.float64)
+                 for s in (n, m + 2)] for _ in range(2))
+    for lvl, F in enumerate(ndgp.total_force(grid, phi, psi)):
+        h = grid.level_h(lvl)
+        for axis in range(3):  # x is the last dimension
+
+            def diff(u):
+                d = torch.roll(u, -1, 2 - axis) - torch.roll(u, 1, 2 - axis)
+                return d[1:-1, 1:-1, 1:-1] if lvl else d
+
+            want = -diff(psi[lvl]) * (0.5 / h) - diff(phi[lvl]) * (0.25 / h)
+            assert float((F[axis] - want).abs().max()) <= 1e-13 * float(want.abs().max())
+
+
 @pytest.mark.parametrize("n,m", [(128, 128), (64, 128), (128, 16)])
 def test_geff_stats_of_levels_a_thread_visits_twice(n, m):
     """128^3 cells are two per thread of the G_eff reduction's fixed grid (fewer cells
