@@ -778,6 +778,22 @@ def test_patch_tile_levels_bitwise_equal_per_level_launches(m, depth, nu1, nu2, 
         assert torch.equal(x, y)
 
 
+@pytest.mark.parametrize("nu1", [4, 6])  # with one sweep after: three launches for four
+@pytest.mark.parametrize("n", [32, 64])
+@pytest.mark.parametrize("precision", [ndgp.PREC_FP64, ndgp.PREC_MIXED])
+def test_tile_levels_two_sweeps_in_a_launch_of_its_own(n, nu1, precision):
+    """An even number of sweeps going down and one going up: a launch of two sweeps that
+    neither adds a correction nor restricts."""
+    test_tile_levels_bitwise_equal_per_level_launches(n, nu1, 1, precision)
+
+
+@pytest.mark.parametrize("m,depth,threshold", [(32, 2, None), (64, 1, None), (32, 2, 0.1),
+                                               (64, 1, 0.1)])
+def test_patch_tile_levels_two_sweeps_in_a_launch_of_its_own(m, depth, threshold):
+    """The same on a refinement, with and without held cells."""
+    test_patch_tile_levels_bitwise_equal_per_level_launches(m, depth, 4, 1, threshold)
+
+
 @pytest.mark.parametrize("n", [8, 16, 32, 64, 128])
 def test_reported_norm_equals_residual_entry_point(n):
     """The norm a solve stops on (added up by the launch's last block up to 256
