@@ -101,10 +101,12 @@ typedef enum {
                               events on `stream` (ndgp_report.t_smooth_ms) */
 #define NDGP_TWO_PASS 4u   /* one launch per colour, per transfer and per level,
                               one thread per cell: no fused one-launch sweep or
-                              LDS-tiled restriction on large levels, no
-                              one-workgroup bottom of the V-cycle on levels of
-                              at most 16^3 cells, and the boxes of a tree solved
-                              one after the other; same results, bit for bit */
+                              LDS-tiled restriction on large levels, no levels
+                              of 16^3 to 64^3 cells swept and restricted tile by
+                              tile, no one-workgroup bottom of the V-cycle where
+                              its coarsest level is below 8^3, and the boxes of
+                              a tree solved one after the other; same results,
+                              bit for bit */
 #define NDGP_DAMPED 8u     /* relax every level with the damped step u + 0.8 du from
                               the start (the mode the divergence safeguard restarts
                               in; ndgp_report.damped_from = 1 on relaxed levels) */
@@ -376,7 +378,10 @@ ndgp_status ndgp_geff_stats(const ndgp_grid *grid, const double *const phi[1 + N
  * particles and the cells by cloud-in-cell).  Particle positions are DEVICE
  * arrays in structure-of-arrays order: pos[0..N) = x, pos[N..2N) = y,
  * pos[2N..3N) = z, in units of the box, each in [0, 1).  A patch compares
- * positions with its cells modulo the box, so patch 1 may wrap the domain.
+ * positions with its cells modulo the box, so patch 1 may wrap the domain; it is
+ * not periodic itself, also where it is as wide as the box (a particle within half
+ * a cell above its lower corner adds nothing to its last cells).  A particle with a
+ * coordinate that is no finite number adds nothing.
  *
  * ndgp_cic_density    delta[l] (natural n^3 / patch_n^3, the layout ndgp_solve
  *                     takes) = count / mean - 1, mean = N / (n 2^l)^3 particles

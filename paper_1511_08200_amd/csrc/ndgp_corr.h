@@ -54,8 +54,9 @@ __device__ __forceinline__ CorrTerms corr_terms(const float vp[19], const float 
     return t;
 }
 
-// New correction at the cell: the root of its own quadratic (same algebra as
-// relax_cell, with w = phi + e in place of phi), discriminant and root in FP64.
+// New correction at the cell: w times the way to the root of its own quadratic (same
+// algebra and cases as relax_cell, with phi + e in place of phi), discriminant and root
+// in FP64.
 __device__ __forceinline__ float relax_corr_cell(const float vp[19], const float ve[19], float r,
                                                  float al, double w, unsigned &fallbacks) {
     const CorrTerms t = corr_terms(vp, ve, al);

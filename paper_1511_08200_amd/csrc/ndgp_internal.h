@@ -417,9 +417,9 @@ struct CicLevels {
     const double *force[kCicMaxLevels];
 };
 // out (3 * np, x then y then z) = cloud-in-cell interpolation of the finest
-// level whose eight cells around the particle lie inside it.  lines (3 n^3
-// doubles; null: not) takes the domain's interleaved components, *lines_off the
-// decision against them.
+// level whose eight cells around the particle lie inside it; out may be pos.  lines
+// (3 n^3 doubles; null: not) takes the domain's interleaved components, *lines_off the
+// device's decision against them, where it has one to make.
 bool cic_gather_lines(long long np, int n);
 void launch_cic_gather(const double *pos, long long np, const CicLevels &lv, double *lines,
                        unsigned *lines_off, double *out, hipStream_t st);

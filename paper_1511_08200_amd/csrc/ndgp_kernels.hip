@@ -3,13 +3,13 @@
 // Every kernel works in cell units (spacing 1 on its level): alpha is
 // alpha_phys / h^2 and the source is h^2 S_phys, so the same code serves all
 // levels.  Equation: Sec. II Eq. (eomvarphi) of arXiv:1511.08200; residual:
-// Eq. (eomgen-disc); relaxation: per-cell root of the cell's own equation, the
-// fixed point of the Newton iteration of Eq. (newton); multigrid transfers:
+// Eq. (eomgen-disc); relaxation: over-relaxed towards the root of the cell's own
+// equation, the fixed point of the Newton iteration of Eq. (newton); multigrid transfers:
 // Sec. III.A; interpolation of refinements: Sec. III.A/III.B; force: Sec. III.B.
 //
 // Memory is HBM-bound everywhere (a few flops per byte, no dense contraction),
-// so nothing here uses MFMA.  Reductions are deterministic: a fixed grid of
-// kReduceBlocks blocks, a fixed per-thread order, in-wave xor-shuffle trees
+// so nothing here uses MFMA.  Reductions are deterministic: a grid of at most
+// kReduceBlocks blocks set by the size, a fixed per-thread order, in-wave xor-shuffle trees
 // and a fixed combination across waves.
 
 #include "ndgp_device.h"

@@ -2,7 +2,7 @@
 //
 // The FP64 outer loop computes r = s - L[phi] and adds corrections to phi.
 // The correction e solves L[phi + e] - L[phi] = r, relaxed here in FP32 with
-// the same red-black per-cell root and full-approximation multigrid as the
+// the same red-black relaxation and full-approximation multigrid as the
 // FP64 path.  An FP32 copy of phi alone cannot carry the solution (its
 // second differences keep only a few of FP32's digits), so the operator is
 // never formed as a difference of two full evaluations: writing w = phi + e,

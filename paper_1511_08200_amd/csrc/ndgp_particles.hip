@@ -36,7 +36,9 @@ __device__ __forceinline__ unsigned long long cic_fixed(double w) {
 }
 
 // distance from the level's lower corner along an axis, modulo the box, in
-// domain cells: [0, n); n is a power of two, so 1 / n scales exactly
+// domain cells: [0, n], n itself where the remainder of a tiny negative distance
+// rounds up to it (its cells and weights are those of distance 0); n is a power of two,
+// so 1 / n scales exactly
 __device__ __forceinline__ double cic_distance(double x01, int n, double corner) {
     const double d = x01 * (double)n - corner;
     return d - (double)n * floor(d * (1.0 / (double)n));
@@ -45,7 +47,9 @@ __device__ __forceinline__ double cic_distance(double x01, int n, double corner)
 // A level and, along one axis, the two neighbouring cells of a particle with
 // their weights: `whole` if both lie in the level (always so on a periodic one).
 // A patch may meet the particle or its image one box further down; where it
-// spans the whole box, its last and first cells are neighbours too.
+// spans the whole box, its last cell's upper neighbour is its first.  (Not the other
+// way: a particle within half a cell above such a patch's lower corner has its lower
+// cell at -1, and that weight is left out, as on any patch's edge.)
 struct CicLevel {
     int n;               // domain cells per side
     double cx, cy, cz;   // the level's lower corner, domain cells

@@ -15,7 +15,7 @@
 // the per-level kernels (k_smooth_half, k_restrict_residual, k_coarse_source,
 // k_prolong8 and their FP32 counterparts), so the result is bit for bit theirs.
 //
-// V(2,2) cycle, us per level (before -> now): 64^3 50 -> 35, 32^3 50 -> 20, 16^3
+// V(2,2) cycle, us per level (per-colour launches -> this): 64^3 50 -> 35, 32^3 50 -> 20, 16^3
 // 33 -> 19, and 9 for the coarsest level's own launch.  Four launches per level
 // is near the floor that launches set; at 64^3 the restricting sweep (14.6 us)
 // is bound by the arithmetic of its halo, 4.4 times the tile's own.
