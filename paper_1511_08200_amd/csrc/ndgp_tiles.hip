@@ -15,10 +15,11 @@
 // the per-level kernels (k_smooth_half, k_restrict_residual, k_coarse_source,
 // k_prolong8 and their FP32 counterparts), so the result is bit for bit theirs.
 //
-// V(2,2) cycle, us per level (per-colour launches -> this): 64^3 50 -> 35, 32^3 50 -> 20, 16^3
-// 33 -> 19, and 9 for the coarsest level's own launch.  Four launches per level
-// is near the floor that launches set; at 64^3 the restricting sweep (14.6 us)
-// is bound by the arithmetic of its halo, 4.4 times the tile's own.
+// V(2,2) cycle, us per level (per-colour launches -> this): 64^3 50 -> 35, 32^3
+// 50 -> 22, 16^3 33 -> 20, and 9 for the coarsest level's own launch.  Four launches
+// per level is near the floor that launches set; at 64^3 the restricting sweep (14.6
+// us; 8 at 32^3, 6 at 16^3) is bound by the arithmetic of its halo, 4.4 times the
+// tile's own.
 //
 // LDS keeps both colours apart, so that lanes on consecutive cells of one
 // colour touch consecutive words.
@@ -282,9 +283,9 @@ void tile_level(const TileArgs<typename P::T> &a, int sweeps, bool pro, bool res
 // ghost shell, the coarse ones with ghosts that follow the interior (dyn), held
 // cells kept.  A cell that changes rewrites its ghosts (write_owned_ghosts) in the
 // step that stores it, from the level's hat values held in LDS beside the field.
-// V(2,2) cycle of a 128^3 refinement's coarse levels, us (before -> now): 64^3 60
-// -> 54, 32^3 55 -> 33, and 62 (one workgroup from 16^3 down) -> 33 + 16 for the
-// coarsest level's own launch.
+// V(2,2) cycle of a 128^3 refinement's coarse levels, us (per-colour launches -> this):
+// 64^3 60 -> 53, 32^3 55 -> 33, and 62 (one workgroup from 16^3 down) -> 30 + 16 for
+// the coarsest level's own launch.
 template <int TILE, int NS, bool PRO, bool REST, int NT>
 __global__ void __launch_bounds__(NT)
 k_tile_dir(TileDirArgs a) {
